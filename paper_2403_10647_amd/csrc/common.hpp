@@ -29,6 +29,9 @@ struct Control {
   uint64_t box_npairs;         // culled builds: the box pair count (npairs then holds the kept count)
   uint32_t tfo_work_n;         // tile-owner runs left for the plan kernel to write
   uint32_t big_n;              // compact builds: cells listed for the workgroup sort
+  uint64_t nitems;             // record builds: records of the build (npairs is then the pairs they hold)
+  uint32_t nlist;              // record builds: segments that hold a record
+  uint32_t ngaps;              // record builds: very long stretches of empty segments
 };
 constexpr uint32_t kErrBadIndex = 1u;
 constexpr uint32_t kErrInternal = 2u;  // an internal consistency check failed (the build's output is invalid)
@@ -45,6 +48,15 @@ GB_DEV uint32_t lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdg
 GB_DEV uint32_t mbcnt(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
+// Orders a wave's LDS accesses: what other lanes stored before is read after.
+// The hardware runs a wave's LDS operations in order; the fences keep the
+// compiler from forwarding a lane's own earlier value past another lane's store.
+GB_DEV void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 GB_DEV uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
@@ -69,6 +81,11 @@ struct OpMax {
   GB_DEV uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
 };
 
+struct OpXor {
+  static constexpr uint32_t identity = 0;
+  GB_DEV uint32_t operator()(uint32_t a, uint32_t b) const { return a ^ b; }
+};
+
 // Inclusive scan across the 64 lanes of a wave (all lanes must be active).
 // row_shr 1/2/4/8 scans each row of 16 lanes; row_bcast 15/31 carries row
 // totals into the rows above.
@@ -88,21 +105,22 @@ GB_DEV uint32_t wave_readlane(uint32_t v, int lane) {
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), lane));
 }
 
-// 64-bit inclusive sum across a wave, through ds_bpermute (not a hot loop).
+// 64-bit inclusive sum across a wave (all lanes active; values and sums below
+// 2^62), as 32-bit scans of the values' low 26, next 26 and last 10 bits, whose
+// sums over 64 lanes need 32, 32 and 16 bits.  Three DPP scans are 18 vector
+// instructions, where 64-bit shuffles take 12 trips through the LDS unit.
 GB_DEV uint64_t wave_inclusive_sum64(uint64_t v) {
-  const uint32_t lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    uint64_t o = __shfl_up(v, d, kWave);
-    if (lane >= static_cast<uint32_t>(d)) v += o;
-  }
-  return v;
+  constexpr uint32_t m = (1u << 26) - 1u;
+  const uint32_t lo = wave_inclusive(static_cast<uint32_t>(v) & m, OpAdd{});
+  const uint32_t mid = wave_inclusive(static_cast<uint32_t>(v >> 26) & m, OpAdd{});
+  const uint32_t hi = wave_inclusive(static_cast<uint32_t>(v >> 52), OpAdd{});
+  return (static_cast<uint64_t>(hi) << 52) + (static_cast<uint64_t>(mid) << 26) + lo;
 }
 
 GB_DEV uint64_t wave_sum64(uint64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-  return v;
+  v = wave_inclusive_sum64(v);
+  return (static_cast<uint64_t>(wave_readlane(static_cast<uint32_t>(v >> 32), kWave - 1)) << 32) |
+         wave_readlane(static_cast<uint32_t>(v), kWave - 1);
 }
 
 // Lanes of the wave whose digit equals this lane's (and that are valid).
@@ -139,7 +157,9 @@ GB_DEV uint64_t status_load(const uint64_t* p) {
 // Decoupled look-back by one full wave over status[tile - 1], status[tile - 2],
 // ... (stride apart).  Publishes the tile's aggregate, returns the exclusive
 // prefix (the sum of every earlier tile) and publishes the inclusive prefix.
-// Every lane returns the same value.
+// Every lane returns the same value.  (64 words a round: four words per lane
+// made fewer rounds of more polls, which slowed the tiles they poll for - the
+// culled expansion's 115K tiles by a third.)
 GB_DEV uint64_t lookback_wave(uint64_t* status, uint32_t tile, uint64_t aggregate) {
   const uint32_t lane = lane_id();
   if (tile == 0) {
@@ -234,7 +254,7 @@ GB_DEV uint64_t lookback_thread(W* status, uint32_t stride, uint32_t col, uint32
 GB_DEV uint32_t next_tile(uint32_t* counter, uint32_t* lds_slot) {
   if (threadIdx.x == 0) *lds_slot = atomicAdd(counter, 1u);
   __syncthreads();
-  const uint32_t t = *lds_slot;
+  const uint32_t t = __builtin_amdgcn_readfirstlane(*lds_slot);  // visibly uniform: what follows from it stays scalar
   __syncthreads();
   return t;
 }
@@ -245,7 +265,7 @@ template <int Block>
 GB_DEV uint32_t block_exclusive_sum(uint32_t v, uint32_t* wave_tot, uint32_t& total) {
   constexpr int kWaves = Block / kWave;
   const uint32_t lane = lane_id();
-  const uint32_t w = threadIdx.x / kWave;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t inc = wave_inclusive(v, OpAdd{});
   if (lane == kWave - 1) wave_tot[w] = inc;
   __syncthreads();
@@ -266,7 +286,7 @@ template <int Block>
 GB_DEV uint32_t block_inclusive_max(uint32_t v, uint32_t* wave_tot) {
   constexpr int kWaves = Block / kWave;
   const uint32_t lane = lane_id();
-  const uint32_t w = threadIdx.x / kWave;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t inc = wave_inclusive(v, OpMax{});
   if (lane == kWave - 1) wave_tot[w] = inc;
   __syncthreads();
@@ -285,7 +305,7 @@ template <int Block>
 GB_DEV uint32_t block_exclusive_max(uint32_t v, uint32_t* wave_tot) {
   constexpr int kWaves = Block / kWave;
   const uint32_t lane = lane_id();
-  const uint32_t w = threadIdx.x / kWave;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t inc = wave_inclusive(v, OpMax{});
   uint32_t ex = __shfl_up(inc, 1, kWave);
   if (lane == 0) ex = 0;
@@ -306,7 +326,7 @@ template <int Block>
 GB_DEV uint64_t block_exclusive_sum64(uint64_t v, uint64_t* wave_tot, uint64_t& total) {
   constexpr int kWaves = Block / kWave;
   const uint32_t lane = lane_id();
-  const uint32_t w = threadIdx.x / kWave;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint64_t inc = wave_inclusive_sum64(v);
   if (lane == kWave - 1) wave_tot[w] = inc;
   __syncthreads();

@@ -19,7 +19,33 @@ struct GridDev {
   uint32_t res[3];
   float lo[3];
   float inv[3];
+  uint32_t sx, sy;         // record builds: a segment is sx cells of sy rows (sy > 1 only where sx is the whole row)
+  uint32_t nsx, nsy;       // segments along x and y (one cell layer in z)
+  uint32_t mgx, mgy;       // 2^20 / sx and 2^20 / sy, rounded up: v / sx = v * mgx >> 20 for every v < 1024
+  uint32_t seg_base;       // first segment of this grid in the batch's segment space
+  uint32_t pad;
 };
+
+// A grid of the batch's table read by a whole wave at once, every word held in
+// a scalar register.  (The compiler keeps table words that stores might alias in
+// vector registers: 30 of them, in kernels that have none to spare.)
+GB_DEV GridDev uniform_grid(const GridDev* p) {
+  constexpr int N = sizeof(GridDev) / 4;
+  static_assert(sizeof(GridDev) % 4 == 0, "copied word by word");
+  union {
+    uint32_t w[N];
+    GridDev g;
+  } u;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(p);
+#pragma unroll
+  for (int i = 0; i < N; ++i) u.w[i] = __builtin_amdgcn_readfirstlane(src[i]);
+  return u.g;
+}
+
+// v / d for v < 1024 and d <= 1024, with m = 2^20 / d rounded up: m * d exceeds
+// 2^20 by less than d, so v * m / 2^20 exceeds v / d by less than
+// v * d / (2^20 * d) <= 1 / d, too little to reach the next whole number.
+GB_DEV uint32_t div_small(uint32_t v, uint32_t m) { return __umul24(v, m) >> 20; }
 
 // Packed cell box of a triangle: lo corner (3 x 10 bits) and extent - 1
 // (3 x 10 bits), so one 64-bit word per triangle.

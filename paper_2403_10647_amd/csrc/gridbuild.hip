@@ -15,6 +15,7 @@
 #include "raycast.hpp"
 #include "kernels.hpp"
 #include "ranges.hpp"
+#include "records.hpp"
 #include "scan.hpp"
 #include "sort.hpp"
 
@@ -32,6 +33,18 @@ constexpr int kSortTile = kSortBlock * kSortK;
 constexpr int kSortTileMin = 4096;                      // smallest tile of any radix-pass or expansion shape
 constexpr int kRangesBlock = 256, kRangesK = 16;        // 4096 merge items per range tile
 constexpr int kMergeTile = kRangesBlock * kRangesK;
+constexpr int kRecordBlock = 1024, kRecordK = 4;        // records: the expansion's tiles in more, shorter runs
+constexpr int kSegListBlock = 1024, kSegListK = 16;     // 16384 records per tile of the segment list
+constexpr int kSegListTile = kSegListBlock * kSegListK;
+constexpr int kFinishMidBlock = 256;
+constexpr uint32_t kFinishMidCap = 4096;                // pairs a small workgroup stages
+// Pairs a wave stages, by the cells of its per-cell tables: segments of up to 64
+// cells are the dense grids' (their pairs per segment spread wider, and their
+// tables leave room for it).
+constexpr uint32_t kFinishCap = 1000, kFinishCapDense = 2000;
+constexpr uint64_t kFinishOnePairs = uint64_t{1} << 18;  // builds of at most this many pairs finish in one launch less
+constexpr int kFinishBigBlock = 1024;
+constexpr uint32_t kFinishBigCap = 12288;               // pairs a workgroup stages
 constexpr int kScanBlock = 256, kScanK = 8;
 constexpr int kMakePairsBlock = 256;                    // per-object pair generation: one thread per object
 constexpr int kPlanBlock = 1024;
@@ -42,6 +55,7 @@ constexpr double kCompactMaxPairsPerCell = 2.0;          // ... at or below this
 constexpr int kMaxRadixBits = 11;
 constexpr int kKeyMapBits = 13;                         // batched key map: at most 8192 buckets
 static_assert((1 << kExpandTileShift) == kExpandTile, "expansion tile must be a power of two");
+static_assert(kRecordBlock * kRecordK == kExpandTile, "records are expanded in the tiles the count marks owners for");
 static_assert(kExpandTile >= kSortTileMin && kSortTile >= kSortTileMin, "tile tables are sized by the smallest tile");
 
 #define GB_TRY(expr)                             \
@@ -192,9 +206,11 @@ Plan make_plan(uint32_t bits, int max_digit = -1) {
 
 struct Layout {
   size_t ctl, hist, count_status, cull_status, cell_status, zero_end;
+  size_t grid_pairs, list_status, list, gaps;  // record builds
   size_t start, box, tfo, tfg, tfo_work, cull_rec, sort_status, keys_alt, vals_alt, keys_alt2, vals_alt2, run, npairs_out, splits,
       tile_grid, table, sink, kmap, ksink, total;
   uint32_t ntfo, ncount_tiles, nsort_tiles_cap, nmerge_tiles_cap;
+  uint32_t list_cap, gap_cap;
 };
 
 Layout make_layout(uint64_t ntris, uint64_t cap_pairs, uint64_t ncells_plus_grids, const Plan& plan,
@@ -237,6 +253,122 @@ Layout make_layout(uint64_t ntris, uint64_t cap_pairs, uint64_t ncells_plus_grid
   L.sink = take(batched ? ngrids * sizeof(GridSink) : 0);
   L.kmap = take(batched ? (size_t{1} << kKeyMapBits) * sizeof(uint2) : 0);
   L.ksink = take(batched ? (size_t{1} << kKeyMapBits) * sizeof(GridSink) : 0);
+  L.total = o + 256;
+  return L;
+}
+
+// Radix passes of fewer pairs than this use 32-bit look-back words (a 30-bit
+// value each): half the stores and polls of 64-bit words.  The wide_lookback
+// knob keeps 64-bit words for every build.
+constexpr uint64_t kNarrowLimit = uint64_t{1} << 30;
+int g_wide_lookback = 0;
+uint32_t narrow_words(uint64_t max_pairs) { return !g_wide_lookback && max_pairs < kNarrowLimit ? 1u : 0u; }
+
+// ---- builds by records -------------------------------------------------------------
+// How a build's grids are cut into segments, and the sort of its records.
+struct RecordPlan {
+  SegCode code;
+  Plan plan;      // digits of the segment, its shifts counted from the key's lowest bit
+};
+
+void set_segments(GridDev& g, uint32_t wx, uint32_t wy) {
+  const uint32_t w = 1u << wx;
+  g.nsx = static_cast<uint32_t>(ceil_div(g.res[0], w));
+  g.sx = static_cast<uint32_t>(ceil_div(g.res[0], g.nsx));
+  g.nsx = static_cast<uint32_t>(ceil_div(g.res[0], g.sx));
+  g.sy = g.nsx == 1 ? std::min(g.res[1], 1u << wy) : 1u;
+  g.nsy = static_cast<uint32_t>(ceil_div(g.res[1], g.sy));
+  g.mgx = ((1u << 20) + g.sx - 1) / g.sx;
+  g.mgy = ((1u << 20) + g.sy - 1) / g.sy;
+}
+
+// Pairs a segment should hold: enough that a wave is not mostly overhead, few
+// enough that nearly all of a scene's segments fit its wave's staging.  Segments
+// of more than 64 cells get half of it, as their staging is half.
+constexpr uint64_t kSegPairs = 384, kSegPairsDense = 768, kSegPairsFew = 48, kFewSegs = 4096;
+
+// Segments for grids of `cells` cells in all (rx, ry: the widest grid's) and
+// about `pairs` pairs: 2^(wx + wy) cells each, whole rows while rows are short.
+// (wider: twice as wide, that many times.)  False when a record would not fit its 64 bits
+// (or a list entry its scan word), or there is nothing wider.
+bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pairs, uint32_t wider, RecordPlan* rp) {
+  uint32_t rx = 1, ry = 1, tmax = 1;
+  for (uint32_t g = 0; g < ngrids; ++g) {
+    rx = std::max(rx, grids[g].res[0]);
+    ry = std::max(ry, grids[g].res[1]);
+    tmax = std::max(tmax, grids[g].ntris);
+  }
+  auto width = [&](uint64_t seg_pairs) {  // log2 of the cells that hold seg_pairs pairs, at most 8
+    const uint64_t want = seg_pairs * cells / std::max<uint64_t>(pairs, 1);
+    uint32_t w = 0;
+    while (w < 8 && (uint64_t{2} << w) <= want) ++w;
+    return w;
+  };
+  uint32_t wb = width(kSegPairsDense);
+  if (wb > 6) wb = std::max(width(kSegPairs), 6u);
+  // few pairs: more, smaller segments, so that no wave holds up a build that the
+  // GPU's waves would have done at once (33K pairs: 122 us at 384 a segment, 86 so)
+  if (pairs < kSegPairs * kFewSegs) wb = std::min(wb, width(std::max(pairs / kFewSegs, kSegPairsFew)));
+  if ((wb += wider) > 8) return false;
+  SegCode c{};
+  c.wx = std::min(wb, bits_for(rx));
+  c.wy = std::min(wb - c.wx, bits_for(ry));
+  uint64_t nsegs = 0;
+  for (uint32_t g = 0; g < ngrids; ++g) {
+    set_segments(grids[g], c.wx, c.wy);
+    grids[g].seg_base = static_cast<uint32_t>(nsegs);
+    nsegs += static_cast<uint64_t>(grids[g].nsx) * grids[g].nsy * grids[g].res[2];
+    if (nsegs >= (uint64_t{1} << 28)) return false;
+  }
+  const uint32_t segbits = bits_for(nsegs), ext = c.wx + c.wy;
+  c.nsegs = static_cast<uint32_t>(nsegs);
+  c.ck = std::min(2 * ext, 32 - segbits);
+  c.objbits = bits_for(tmax);
+  if (c.ck < ext || 2 * ext - c.ck > 32 - c.objbits) return false;
+  rp->code = c;
+  rp->plan = make_plan(segbits);
+  for (uint32_t p = 0; p < rp->plan.sp.passes; ++p) rp->plan.sp.shift[p] += c.ck;
+  return true;
+}
+
+// Workspace of a build by records.  It takes no more than make_layout's for the
+// same build except for its list of segments, so a build runs by records where
+// that fits what the caller was asked for.
+Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& rp, uint32_t ngrids, bool batched) {
+  Layout L{};
+  size_t o = 0;
+  auto take = [&](size_t bytes) {
+    size_t at = o;
+    o = align_up(o + std::max<size_t>(bytes, 1));
+    return at;
+  };
+  L.ncount_tiles = static_cast<uint32_t>(ceil_div(ntris, kCountBlock * kCountK));
+  L.nsort_tiles_cap = static_cast<uint32_t>(ceil_div(cap_pairs, kSortTileMin));
+  L.ntfo = L.nsort_tiles_cap + 1;
+  L.list_cap = static_cast<uint32_t>(std::min<uint64_t>(rp.code.nsegs, cap_pairs));
+  L.gap_cap = rp.code.nsegs / (kGapBlock >> (rp.code.wx + rp.code.wy)) + 2;
+  L.ctl = take(sizeof(Control));
+  L.hist = take(static_cast<size_t>(kHistCopies) * 4 * kRadixMax * sizeof(uint32_t));
+  L.count_status = take(std::max<size_t>(L.ncount_tiles, 1) * 8);
+  L.grid_pairs = take(static_cast<size_t>(ngrids) * 8);
+  L.list_status = take((ceil_div(cap_pairs, kSegListTile) + 1) * 8);
+  L.zero_end = o;
+  L.start = take(ntris * 4);
+  L.box = take(ntris * 8);
+  L.tfo = take(static_cast<size_t>(L.ntfo) * 4);
+  L.tfg = take(batched ? static_cast<size_t>(L.ntfo) * 4 : 0);
+  L.tfo_work = take(tfo_work_cap(L.ntfo) * sizeof(uint4));
+  L.sort_status = take(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
+                       (narrow_words(cap_pairs) ? 4 : 8));
+  L.keys_alt = take(cap_pairs * 4);
+  L.vals_alt = take(cap_pairs * 4);
+  L.keys_alt2 = take(batched ? cap_pairs * 4 : 0);
+  L.vals_alt2 = take(batched ? cap_pairs * 4 : 0);
+  L.run = take((ngrids + 1) * sizeof(GridRun));
+  L.npairs_out = take((ngrids + 1) * 8);
+  L.table = take(batched ? ngrids * sizeof(GridDev) : 0);
+  L.list = take((static_cast<size_t>(L.list_cap) + 1) * sizeof(SegEntry));
+  L.gaps = take(static_cast<size_t>(L.gap_cap) * 3 * 4);
   L.total = o + 256;
   return L;
 }
@@ -312,7 +444,40 @@ struct Build {
   uint64_t layout_cap = ~uint64_t{0};  // pairs the workspace layout holds, checked by the plan
   bool no_alloc = false;  // the build may not allocate, not even host memory for its readback
   int sort_shape = 3;     // tile shape of the radix passes from arrays (build_sort_shape)
+  bool rec = false;       // the build sorts records (records.hpp), not pairs
+  SegCode code{};
+  uint64_t rec_cap = 0;   // ... and the launches' pair capacity
 };
+
+// Whether a sorted build under the current knobs may run by records: the knobs
+// that choose another pair generation are about the pairs themselves.
+bool records_allowed() { return g_build_path == 0 && !g_fused_expand && !g_per_object_pairs; }
+
+// Builds by records from this many pairs, and below it from this many pairs a
+// triangle: a box of one or two cells is about as many records as pairs, and the
+// records' extra steps then cost more than their passes save.  Measured, us by
+// pairs and by records: 4.3M pairs at 2.2 a triangle 199 and 294, 2.1M at 2.1 161
+// and 180, 4.3M at 4.3 196 and 173, 3.5M at 3.5 201 and 176, 54M at 5.4 1190 and
+// 860, 30M at 30 635 and 302; up to 2^18 pairs the two are within 4%.
+constexpr uint64_t kRecordsFew = uint64_t{1} << 18;
+bool records_pay(uint64_t pairs, uint64_t ntris) { return pairs <= kRecordsFew || 4 * pairs >= 13 * ntris; }
+
+// Makes b a build by records when its grids, about `pairs` pairs, allow it and the workspace holds it.
+void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t cap, uint64_t pairs, size_t ws_bytes) {
+  if (b.ntris == 0 || cap == 0 || !records_pay(pairs, b.ntris)) return;
+  RecordPlan rp{};
+  Layout L{};
+  // a workspace too small for the list of segments: wider segments, fewer of them
+  for (uint32_t wider = 0;; ++wider) {
+    if (!plan_records(grids, ngrids, cells, pairs, wider, &rp)) return;
+    L = make_record_layout(b.ntris, cap, rp, ngrids, b.batched);
+    if (L.total <= ws_bytes) break;
+  }
+  b.rec = true;
+  b.code = rp.code;
+  b.plan = rp.plan;
+  b.L = L;
+}
 
 template <bool B>
 int launch_count(Build& b) {
@@ -330,8 +495,10 @@ int launch_count(Build& b) {
   a.tfo_work = at<uint4>(b.ws, b.L.tfo_work);
   a.tfo_work_cap = tfo_work_cap(b.L.ntfo);
   a.ctl = at<Control>(b.ws, b.L.ctl);
+  a.grid_pairs = at<uint64_t>(b.ws, b.L.grid_pairs);
   TraceScope ts(b.s, "count_scan");
-  count_kernel<kCountBlock, kCountK, B><<<b.L.ncount_tiles, kCountBlock, 0, b.s>>>(a);
+  if (b.rec) count_kernel<kCountBlock, kCountK, B, true><<<b.L.ncount_tiles, kCountBlock, 0, b.s>>>(a);
+  else count_kernel<kCountBlock, kCountK, B><<<b.L.ncount_tiles, kCountBlock, 0, b.s>>>(a);
   GB_LAUNCHED();
   return GRID_OK;
 }
@@ -352,8 +519,10 @@ int launch_plan(Build& b) {
   a.tfo_work = at<uint4>(b.ws, b.L.tfo_work);
   a.tfo_work_cap = tfo_work_cap(b.L.ntfo);
   a.ctl = at<Control>(b.ws, b.L.ctl);
+  a.grid_pairs = at<uint64_t>(b.ws, b.L.grid_pairs);
   TraceScope ts(b.s, "plan");
-  plan_kernel<kPlanBlock, B><<<1, kPlanBlock, 0, b.s>>>(a);
+  if (b.rec) plan_kernel<kPlanBlock, B, true><<<1, kPlanBlock, 0, b.s>>>(a);
+  else plan_kernel<kPlanBlock, B><<<1, kPlanBlock, 0, b.s>>>(a);
   GB_LAUNCHED();
   return GRID_OK;
 }
@@ -424,6 +593,10 @@ StatusClear status_clear(const Build& b, int RB) {
   c.status = at<uint64_t>(b.ws, b.L.sort_status);
   c.stride = static_cast<uint64_t>(b.L.nsort_tiles_cap) * (RB > 0 ? (1u << RB) : 1u);
   c.passes = RB > 0 ? b.plan.sp.passes : 0;
+  if (b.rec && narrow_words(b.rec_cap)) {
+    c.halves = 1;
+    c.stride >>= 1;
+  }
   for (uint32_t p = 0; p < c.passes; ++p) {
     c.tile[p] = pass_tile(b, p);
     c.radix[p] = 1u << pass_bits(b.plan.sp.width[p]);
@@ -683,13 +856,6 @@ int launch_sink(Build& b) {
   return GRID_OK;
 }
 
-// Radix passes of fewer pairs than this use 32-bit look-back words (a 30-bit
-// value each): half the stores and polls of 64-bit words.  The wide_lookback
-// knob keeps 64-bit words for every build.
-constexpr uint64_t kNarrowLimit = uint64_t{1} << 30;
-int g_wide_lookback = 0;
-uint32_t narrow_words(uint64_t max_pairs) { return !g_wide_lookback && max_pairs < kNarrowLimit ? 1u : 0u; }
-
 template <int RB, bool B>
 int launch_sort_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t npairs) {
   const SortPlan& sp = b.plan.sp;
@@ -787,6 +953,157 @@ int launch_sort(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t npai
     case 9: return launch_sort_rb<9, B>(b, out_cells, out_objs, npairs);
     case 10: return launch_sort_rb<10, B>(b, out_cells, out_objs, npairs);
     case 11: return launch_sort_rb<11, B>(b, out_cells, out_objs, npairs);
+    default: return GRID_E_INVAL;
+  }
+}
+
+// A build by records, after its count and plan: records, radix passes over
+// their segments, the list of segments, and each segment's pairs and ranges.
+// Writer i of the sequence (i = -1: the records, then the passes) alternates
+// between two buffers so that the last one is the workspace's first; the other
+// is the caller's outputs (plain) or the workspace's second (batched).
+template <int RB, bool B>
+int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t npairs) {
+  const SortPlan& sp = b.plan.sp;
+  Control* ctl = at<Control>(b.ws, b.L.ctl);
+  const uint32_t P = sp.passes;
+  b.sort_shape = build_sort_shape(npairs / 2);
+  b.rec_cap = npairs;
+  const Dest bufs[2] = {{at<uint32_t>(b.ws, b.L.keys_alt), at<uint32_t>(b.ws, b.L.vals_alt)},
+                        B ? Dest{at<uint32_t>(b.ws, b.L.keys_alt2), at<uint32_t>(b.ws, b.L.vals_alt2)}
+                          : Dest{out_cells, out_objs}};
+  if (!bufs[1].k || !bufs[1].v) return GRID_E_INVAL;
+  Dest d = bufs[P % 2];
+  {
+    RecordArgs a{};
+    a.o.ex = expand_args(b);
+    a.o.cells = d.k;
+    a.o.objs = d.v;
+    a.o.plan = sp;
+    a.o.hist = at<uint32_t>(b.ws, b.L.hist);
+    a.o.clear = status_clear(b, RB);
+    a.o.vec16 = ((reinterpret_cast<uintptr_t>(d.k) | reinterpret_cast<uintptr_t>(d.v)) & 15u) == 0;
+    a.o.ctl = ctl;
+    a.code = b.code;
+    a.run = at<GridRun>(b.ws, b.L.run);
+    {
+      TraceScope ts(b.s, "records");
+      auto kern = record_kernel<kRecordBlock, kRecordK, RB, B>;
+      kern<<<resident_blocks(kern, kRecordBlock, ceil_div(npairs, kExpandTile)), kRecordBlock, 0, b.s>>>(a);
+      GB_LAUNCHED();
+    }
+    if constexpr (B) {
+      if (b.gs.ngrids >= 2) {
+        TraceScope ts(b.s, "records_straddle");
+        auto kern = record_straddle_kernel<kExpandBlock, kExpandK, RB>;
+        kern<<<static_cast<uint32_t>(std::min<uint64_t>(ceil_div(npairs, kExpandTile), 1024)), kExpandBlock, 0, b.s>>>(a);
+        GB_LAUNCHED();
+      }
+    }
+  }
+  {
+    TraceScope span(b.s, "radix_passes", true);
+    for (uint32_t p = 0; p < P; ++p) {
+      SortPassArgs a{};
+      a.keys_in = d.k;
+      a.vals_in = d.v;
+      d = bufs[(P - 1 - p) % 2];
+      a.keys_out = d.k;
+      a.vals_out = d.v;
+      a.ex = expand_args(b);
+      a.hist = at<uint32_t>(b.ws, b.L.hist) + p * kRadixMax;
+      a.hist_copies = kHistCopies;
+      a.hist_stride = 4 * kRadixMax;
+      a.narrow = narrow_words(npairs);
+      a.status = at<uint64_t>(b.ws, b.L.sort_status) +
+                 ((static_cast<uint64_t>(p) * b.L.nsort_tiles_cap * (1u << RB)) >> (a.narrow ? 1 : 0));
+      a.n = npairs;
+      a.n_from_ctl = 2;
+      a.shift = sp.shift[p];
+      a.width = sp.width[p];
+      a.counter = kCtrSort0 + p;
+      a.ctl = ctl;
+      TraceScope ts(b.s, "onesweep");
+      int st = launch_pass<false>(a, pass_bits(sp.width[p]), false, false,
+                                  static_cast<uint32_t>(ceil_div(npairs, sort_shape_tile(b.sort_shape))), b.s, b.sort_shape);
+      if (st) return st;
+    }
+  }
+  SegEntry* const sl = at<SegEntry>(b.ws, b.L.list);
+  {
+    SegListArgs a{};
+    a.keys = bufs[0].k;
+    a.code = b.code;
+    a.list = sl;
+    a.list_cap = b.L.list_cap;
+    a.status = at<uint64_t>(b.ws, b.L.list_status);
+    a.vec16 = (reinterpret_cast<uintptr_t>(a.keys) & 15u) == 0;
+    a.ctl = ctl;
+    TraceScope ts(b.s, "seg_list");
+    auto kern = seg_list_kernel<kSegListBlock>;
+    kern<<<resident_blocks(kern, kSegListBlock, ceil_div(npairs, kSegListTile)), kSegListBlock, 0, b.s>>>(a);
+    GB_LAUNCHED();
+  }
+  FinishArgs a{};
+  a.gs = b.gs;
+  a.run = at<GridRun>(b.ws, b.L.run);
+  a.keys = bufs[0].k;
+  a.vals = bufs[0].v;
+  a.code = b.code;
+  a.list = sl;
+  a.list_cap = b.L.list_cap;
+  a.gaps = at<uint32_t>(b.ws, b.L.gaps);
+  a.gap_cap = b.L.gap_cap;
+  a.ctl = ctl;
+  // the LDS per-cell tables are sized for the segments' width
+  const uint32_t bits = b.code.wx + b.code.wy;
+  const uint32_t wave_cap = bits <= 6 ? kFinishCapDense : kFinishCap;
+  {
+    TraceScope ts(b.s, "finish");
+    auto kern = bits <= 6 ? (b.code.wy ? finish_kernel<kFinishCapDense, 64, B, true> : finish_kernel<kFinishCapDense, 64, B, false>)
+              : bits <= 7 ? (b.code.wy ? finish_kernel<kFinishCap, 128, B, true> : finish_kernel<kFinishCap, 128, B, false>)
+                          : (b.code.wy ? finish_kernel<kFinishCap, 256, B, true> : finish_kernel<kFinishCap, 256, B, false>);
+    kern<<<static_cast<uint32_t>(ceil_div(b.L.list_cap, kFinishRun)), kWave, 0, b.s>>>(a);
+    GB_LAUNCHED();
+  }
+  {
+    // few pairs: one launch for all that is left (a workgroup that meets more than
+    // its staging holds stores pairs where their ranks put them)
+    const bool all = npairs <= kFinishOnePairs;
+    TraceScope ts(b.s, "finish_mid");
+    auto kern = all ? (b.code.wy ? finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, true, B, true>
+                                 : finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, true, B, false>)
+                    : (b.code.wy ? finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, false, B, true>
+                                 : finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, false, B, false>);
+    kern<<<resident_blocks(kern, kFinishMidBlock, b.L.list_cap), kFinishMidBlock, 0, b.s>>>(a, wave_cap, all ? 0xFFFFFFFFu : kFinishMidCap);
+    GB_LAUNCHED();
+    if (all) return GRID_OK;
+  }
+  {
+    TraceScope ts(b.s, "finish_big");
+    auto kern = b.code.wy ? finish_big_kernel<kFinishBigBlock, kFinishBigCap, false, true, B, true>
+                          : finish_big_kernel<kFinishBigBlock, kFinishBigCap, false, true, B, false>;
+    kern<<<static_cast<uint32_t>(device_cus()), kFinishBigBlock, 0, b.s>>>(a, kFinishMidCap, 0xFFFFFFFFu);
+    GB_LAUNCHED();
+  }
+  return GRID_OK;
+}
+
+bool record_plan_ok(const Plan& p) {
+  if (p.sp.passes > 4 || p.rb < 8 || p.rb > kMaxRadixBits) return false;
+  for (uint32_t i = 0; i < p.sp.passes; ++i)
+    if (p.sp.width[i] < 1 || static_cast<int>(p.sp.width[i]) > p.rb || p.sp.shift[i] + p.sp.width[i] > 32) return false;
+  return true;
+}
+
+template <bool B>
+int launch_records(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t npairs) {
+  if (!record_plan_ok(b.plan)) return GRID_E_INVAL;
+  switch (b.plan.rb) {
+    case 8: return launch_records_rb<8, B>(b, out_cells, out_objs, npairs);
+    case 9: return launch_records_rb<9, B>(b, out_cells, out_objs, npairs);
+    case 10: return launch_records_rb<10, B>(b, out_cells, out_objs, npairs);
+    case 11: return launch_records_rb<11, B>(b, out_cells, out_objs, npairs);
     default: return GRID_E_INVAL;
   }
 }
@@ -953,6 +1270,8 @@ int build_plain(const float* verts_soa, uint32_t nverts, const uint32_t* tris, u
   int st = prepare_plain(b, verts_soa, nverts, tris, ntris, lo, hi, res, ws, ws_bytes, out->cap_pairs, stream);
   if (st) return st;
   b.no_alloc = no_alloc;
+  if (records_allowed())
+    try_records(b, &b.gs.one, 1, ncells_of(res), out->cap_pairs, out->cap_pairs, ws_bytes);
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
   b.gs.one.out_ranges = out->ranges;
@@ -972,12 +1291,14 @@ int build_plain(const float* verts_soa, uint32_t nverts, const uint32_t* tris, u
   g_last_path = path;
   if (path == 1) {
     if ((st = launch_compact(b, out))) return st;
+  } else if (b.rec) {
+    if ((st = launch_records<false>(b, out->cells, out->objs, cap))) return st;
   } else if (b.plan.sp.passes == 0) {
     if ((st = launch_expand<0, false>(b, out->cells, out->objs, cap))) return st;
   } else if (cap > 0) {
     if ((st = launch_sort<false>(b, out->cells, out->objs, cap))) return st;
   }
-  if (path != 1 && (st = launch_ranges<false>(b, ncells_of(res) + 1 + cap))) return st;
+  if (path != 1 && !b.rec && (st = launch_ranges<false>(b, ncells_of(res) + 1 + cap))) return st;
   HostCtl h{};
   if ((st = read_ctl(b, &h))) return st;
   out->npairs = h.npairs;
@@ -1163,6 +1484,9 @@ uint32_t batch_chunk(const grid_desc* grids, uint32_t ngrids, uint32_t g0) {
 constexpr int64_t kCapFromDescs = -1;
 constexpr int64_t kCapFromWorkspace = -2;
 
+// Pairs per triangle assumed where a build's pair count is not known yet.
+constexpr uint64_t kPairsPerTriangle = 6;
+
 // Largest pair capacity whose batched layout fits in ws_bytes (-1: not even an empty one).
 int64_t batch_pair_capacity(const BatchSetup& bs, uint32_t ngrids, size_t ws_bytes) {
   const Plan plan = make_plan(std::max(1u, bits_for(bs.cells)));
@@ -1187,7 +1511,7 @@ bool same_geometry(const GridDev& a, const GridDev& b) {
 // which the new table must match grid for grid before anything is enqueued.
 int prepare_batched(Build& b, BatchSetup& bs, const grid_desc* grids, uint32_t ngrids, void* ws, size_t ws_bytes,
                     hipStream_t s, bool need_out, void* staging = nullptr, size_t staging_bytes = 0,
-                    int64_t layout = kCapFromDescs, const GridDev* counted = nullptr) {
+                    int64_t layout = kCapFromDescs, const GridDev* counted = nullptr, bool count_only = false) {
   int st = setup_batch(grids, ngrids, &bs, need_out);
   if (st) return st;
   if (bs.cells > kMaxBatchCells) return GRID_E_INVAL;
@@ -1211,6 +1535,12 @@ int prepare_batched(Build& b, BatchSetup& bs, const grid_desc* grids, uint32_t n
   b.batch_cells = bs.cells;
   b.L = make_layout(bs.ntris, cap, bs.cells + ngrids, b.plan, ngrids, true);
   if (ws_bytes < b.L.total) return GRID_E_NOMEM;
+  if (!count_only && !g_fused_expand) {
+    // a build split around its count knows only the triangles when it cuts the
+    // grids into segments, and both halves must cut them alike
+    const uint64_t pairs = layout == kCapFromWorkspace ? std::min<uint64_t>(cap, kPairsPerTriangle * bs.ntris) : cap;
+    try_records(b, bs.table.data(), ngrids, bs.cells, cap, pairs, ws_bytes);
+  }
   b.gs = GridSet{};
   b.gs.table = at<GridDev>(ws, b.L.table);
   b.gs.ngrids = ngrids;
@@ -1270,7 +1600,8 @@ int grid_count_batched(grid_desc* grids, uint32_t ngrids, void* ws, size_t ws_by
     const uint32_t n = batch_chunk(grids, ngrids, g0);
     Build b{};
     BatchSetup bs;
-    int st = prepare_batched(b, bs, grids + g0, n, ws, ws_bytes, static_cast<hipStream_t>(stream), false);
+    int st = prepare_batched(b, bs, grids + g0, n, ws, ws_bytes, static_cast<hipStream_t>(stream), false, nullptr, 0,
+                             kCapFromDescs, nullptr, true);
     if (st) return st;
     std::vector<uint64_t> np;
     HostCtl h{};
@@ -1300,6 +1631,11 @@ int grid_build_batched(grid_desc* grids, uint32_t ngrids, void* ws, size_t ws_by
       if (np[g] > grids[g0 + g].out.cap_pairs) cap_ok = false;
     }
     if (!cap_ok) return GRID_E_CAPACITY;
+    if (b.rec) {
+      if ((st = launch_records<true>(b, nullptr, nullptr, h.npairs))) return st;
+      g0 += n;
+      continue;
+    }
     if (h.npairs > 0) {
       if (b.plan.sp.passes == 0) return GRID_E_INVAL;  // cannot happen: the grid bits alone need a pass
       if ((st = launch_sort<true>(b, nullptr, nullptr, h.npairs))) return st;
@@ -1614,6 +1950,7 @@ int grid_build_batched_async(const grid_desc* grids, uint32_t ngrids, void* ws, 
   if ((st = launch_count<true>(b))) return st;
   if ((st = launch_plan<true>(b))) return st;
   // sizes on the host are the capacities; the kernels read the true counts
+  if (b.rec) return launch_records<true>(b, nullptr, nullptr, bs.cap);
   if (bs.cap > 0) {
     if (b.plan.sp.passes == 0) return GRID_E_INVAL;
     if ((st = launch_sort<true>(b, nullptr, nullptr, bs.cap))) return st;
@@ -1659,6 +1996,7 @@ int grid_build_batched_counted(const grid_desc* grids, uint32_t ngrids, void* ws
   // a grid beyond its capacity is caught by the sink kernel, pairs beyond the
   // workspace by the count's plan, and either way no kernel writes anything
   const uint64_t n = std::min<uint64_t>(bs.cap, b.layout_cap);
+  if (b.rec) return launch_records<true>(b, nullptr, nullptr, std::max<uint64_t>(n, 1));
   if (n > 0) {
     if (b.plan.sp.passes == 0) return GRID_E_INVAL;
     if ((st = launch_sort<true>(b, nullptr, nullptr, n))) return st;

@@ -50,6 +50,7 @@ struct StatusClear {
   uint32_t tile[4];
   uint32_t radix[4];
   uint32_t passes;
+  uint32_t halves;          // 1: every pass uses 32-bit words, two to each 64-bit word cleared
 };
 
 template <int Block>
@@ -57,7 +58,7 @@ GB_DEV void clear_status(const StatusClear& c, uint64_t npairs) {
   const uint64_t first = static_cast<uint64_t>(blockIdx.x) * Block + threadIdx.x;
   const uint64_t step = static_cast<uint64_t>(gridDim.x) * Block;
   for (uint32_t p = 0; p < c.passes; ++p) {
-    const uint64_t words = ((npairs + c.tile[p] - 1) / c.tile[p]) * c.radix[p];
+    const uint64_t words = (((npairs + c.tile[p] - 1) / c.tile[p]) * c.radix[p]) >> c.halves;  // radix is even
     uint64_t* st = c.status + p * c.stride;
     for (uint64_t i = first; i < words; i += step) st[i] = 0;
   }
@@ -78,6 +79,7 @@ struct CountArgs {
   uint64_t* status;         // [count tiles] look-back words
   uint4* tfo_work;          // [tfo_work_cap] (object, grid, first entry, last entry) runs left for the plan kernel
   uint32_t tfo_work_cap;
+  uint64_t* grid_pairs;     // record builds: [ngrids] each grid's pair count (zeroed), added up per tile
   Control* ctl;
 };
 
@@ -105,18 +107,51 @@ GB_DEV uint32_t grid_of_tri_wave(const GridSet& s, uint32_t t) {
 // per-triangle walk for batched tiles that straddle grids.
 enum CountMode : int { kCountPlain = 0, kCountOneGrid = 1, kCountPerItem = 2 };
 
-// CountCells for the tile's triangles base + k * Block + tid: writes each box
-// and leaves the counts in s_val (striped order).
-template <int Block, int K, int Mode>
-GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, uint32_t* s_val, uint32_t g0 = 0) {
+// Sum over the wave of one count per lane, each below 2^34, in two halves that
+// a 32-bit scan holds (the lanes' low 20 bits sum below 2^26).
+GB_DEV uint64_t wave_sum34(uint64_t v) {
+  const uint32_t lo = wave_inclusive(static_cast<uint32_t>(v) & 0xFFFFFu, OpAdd{});
+  const uint32_t hi = wave_inclusive(static_cast<uint32_t>(v >> 20), OpAdd{});
+  return (static_cast<uint64_t>(wave_readlane(hi, kWave - 1)) << 20) + wave_readlane(lo, kWave - 1);
+}
+GB_DEV void add_u64(uint64_t* p, uint64_t v) {
+  atomicAdd(reinterpret_cast<unsigned long long*>(p), static_cast<unsigned long long>(v));
+}
+
+// Grids of a straddling tile whose pairs are added up in LDS before they reach
+// the grids' totals: global atomic adds on one line cost 14 ns each, one after
+// another (the 512-grid batch's count took 85 us less for it).
+constexpr uint32_t kTileGrids = 64;
+
+// Pairs of the lanes' triangles added to their grids' totals (tiles that
+// straddle grids, the first of them g0): one add per wave when its triangles
+// lie in one grid.
+GB_DEV void add_grid_pairs(uint64_t* grid_pairs, uint64_t* s_pairs, uint32_t g0, uint32_t g, uint64_t pairs) {
+  const uint32_t gf = __builtin_amdgcn_readfirstlane(g);
+  if (ballot(g != gf) == 0) {
+    const uint64_t sum = wave_sum34(pairs);
+    if (lane_id() == 0 && sum) add_u64(gf - g0 < kTileGrids ? s_pairs + (gf - g0) : grid_pairs + gf, sum);
+  } else if (pairs) {
+    add_u64(g - g0 < kTileGrids ? s_pairs + (g - g0) : grid_pairs + g, pairs);
+  }
+}
+
+// CountCells for the tile's triangles base + (k0 + k) * Block + tid: writes each box
+// and leaves the counts in s_val (striped order).  Rec: what is counted (and
+// later expanded and sorted) are the triangle's records, one per segment its
+// box meets; its pairs are only added up, per tile into s_pairs[0] (LDS) or, in
+// tiles that straddle grids, per grid from g0 on.
+template <int Block, int K, int Mode, bool Rec>
+GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, uint32_t* s_val, uint64_t* s_pairs, uint32_t g0 = 0, uint32_t k0 = 0) {
   const uint32_t tid = threadIdx.x;
+  uint64_t pairs = 0;
   uint32_t g = g0;  // kCountPerItem: the grid of the tile's first triangle, walked forward per item
 
   // all index loads, then all vertex loads, then the arithmetic
   uint32_t gi[K], idx[K][3];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const uint64_t t = base + static_cast<uint64_t>(k) * Block + tid;
+    const uint64_t t = base + static_cast<uint64_t>(k0 + k) * Block + tid;
     const uint32_t tc = static_cast<uint32_t>(t < a.ntris ? t : a.ntris - 1);
     if constexpr (Mode == kCountPerItem) g = grid_of_tri<true>(a.gs, tc, g);
     gi[k] = g;
@@ -152,8 +187,9 @@ GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, ui
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const uint64_t t = base + static_cast<uint64_t>(k) * Block + tid;
+    const uint64_t t = base + static_cast<uint64_t>(k0 + k) * Block + tid;
     uint32_t cnt = 0;
+    uint64_t item_pairs = 0;
     if (t < a.ntris) {
       const GridDev& G = Mode == kCountPerItem ? a.gs.table[gi[k]] : G0;
       uint64_t packed = 0;
@@ -173,20 +209,33 @@ GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, ui
         }
         cnt = m[0] * m[1] * m[2];
         packed = pack_box(lo, m);
+        if constexpr (Rec) {
+          if constexpr (Mode != kCountPerItem) pairs += cnt;
+          else item_pairs = cnt;
+          cnt = (div_small(lo[0] + m[0] - 1, G.mgx) - div_small(lo[0], G.mgx) + 1) *
+                (div_small(lo[1] + m[1] - 1, G.mgy) - div_small(lo[1], G.mgy) + 1) * m[2];
+        }
       }
       a.box[t] = packed;
     }
-    s_val[pad32(k * Block + tid)] = cnt;
+    if constexpr (Rec && Mode == kCountPerItem) add_grid_pairs(a.grid_pairs, s_pairs, g0, gi[k], item_pairs);
+    s_val[pad32((k0 + k) * Block + tid)] = cnt;
+  }
+  if constexpr (Rec && Mode != kCountPerItem) {
+    const uint64_t sum = wave_sum34(pairs);
+    if (lane_id() == 0) add_u64(s_pairs, sum);
   }
 }
 
-template <int Block, int K, bool Batched>
+template <int Block, int K, bool Batched, bool Rec = false>
 __global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
   constexpr int Tile = Block * K;
   __shared__ uint32_t s_val[padded(Tile)];
   __shared__ uint64_t s_wtot[Block / kWave];
   __shared__ uint64_t s_prefix;
+  __shared__ uint64_t s_pairs[Rec ? (Batched ? kTileGrids : 1u) : 1u];
   __shared__ uint32_t s_tile;
+  if (Rec && threadIdx.x < (Batched ? kTileGrids : 1u)) s_pairs[threadIdx.x] = 0;
   const uint32_t tile = next_tile(&a.ctl->tile_counter[kCtrCount], &s_tile);
   const uint32_t tid = threadIdx.x;
   const uint64_t base = static_cast<uint64_t>(tile) * Tile;
@@ -203,15 +252,25 @@ __global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
     one = gl + 1 >= a.gs.ngrids || a.gs.table[gl + 1].tri_base > t1;
     if (one) {
       const GridDev G = a.gs.table[gl];
-      count_items<Block, K, kCountOneGrid>(a, G, base, s_val);
+      count_items<Block, K, kCountOneGrid, Rec>(a, G, base, s_val, s_pairs, gl);
     } else {
-      count_items<Block, K, kCountPerItem>(a, a.gs.table[gl], base, s_val, gl);
+      // four triangles at a time: each carries its own grid's parameters, and all
+      // eight at once would spill
+#pragma unroll 1
+      for (uint32_t k0 = 0; k0 < static_cast<uint32_t>(K); k0 += 4)
+        count_items<Block, 4, kCountPerItem, Rec>(a, a.gs.table[gl], base, s_val, s_pairs, gl, k0);
     }
   } else {
-    count_items<Block, K, kCountPlain>(a, a.gs.one, base, s_val);
+    count_items<Block, K, kCountPlain, Rec>(a, a.gs.one, base, s_val, s_pairs);
   }
   __syncthreads();
 
+  if constexpr (Rec) {
+    if (tid < (one ? 1u : kTileGrids)) {
+      const uint64_t p = s_pairs[tid];
+      if (p) add_u64(a.grid_pairs + gl + tid, p);
+    }
+  }
   uint32_t mine[K];
   uint64_t sum = 0;
 #pragma unroll
@@ -225,7 +284,7 @@ __global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
     const uint64_t p = lookback_wave(a.status, tile, total);
     if (tid == 0) {
       s_prefix = p;
-      if (tile == ntiles - 1) a.ctl->npairs = p + total;
+      if (tile == ntiles - 1) (Rec ? a.ctl->nitems : a.ctl->npairs) = p + total;  // (the plan adds up a record build's pairs)
     }
   }
   __syncthreads();
@@ -354,28 +413,28 @@ GB_DEV uint32_t item_slot(uint32_t tid, int k) {
   else return (tid / kWave) * (kWave * K) + k * kWave + (tid % kWave);
 }
 
+// The owners of a tile's slots, K consecutive slots per thread: sv[k] =
+// (object offset from the tile's first object t0) << 16 | the owner's first slot
+// (0 | 0 for t0 itself, which may start before the tile: at global slot s0).
 // s_slot must hold padded(Block * K) words.  Returns the tile's item count.
-// OneGrid: the caller guarantees that the tile's objects lie in one grid.
-// coords (optional, blocked single-grid tiles only): each item's cell
-// coordinates packed as x | y << 10 | z << 20.
-template <int Block, int K, bool Batched, int Layout = kStriped, bool OneGrid = false>
-GB_DEV uint32_t expand_tile(const ExpandArgs& a, uint32_t tile, uint64_t npairs, uint32_t ntiles, uint32_t* s_slot,
-                            uint32_t* s_wtot, uint32_t (&keys)[K], uint32_t (&vals)[K], uint32_t* coords = nullptr) {
+template <int Block, int K>
+GB_DEV uint32_t tile_owners(const ExpandArgs& a, uint32_t tile, uint64_t nitems, uint32_t ntiles, uint32_t* s_slot,
+                            uint32_t* s_wtot, uint32_t (&sv)[K], uint32_t& t0, uint32_t& s0) {
   constexpr int N = Block * K;
   static_assert(N <= 65536, "slot and object offsets are packed in 16 bits");
   constexpr int kHeadBatch = 4;
   const uint32_t tid = threadIdx.x;
   const uint64_t base = static_cast<uint64_t>(tile) * N;
-  const uint32_t n = static_cast<uint32_t>(npairs - base < N ? npairs - base : N);
-  const uint32_t t0 = a.tfo[tile];
-  uint32_t thi = tile + 1 < ntiles ? a.tfo[tile + 1] : a.ntris - 1;
+  const uint32_t n = static_cast<uint32_t>(nitems - base < N ? nitems - base : N);
+  t0 = __builtin_amdgcn_readfirstlane(a.tfo[tile]);
+  uint32_t thi = __builtin_amdgcn_readfirstlane(tile + 1 < ntiles ? a.tfo[tile + 1] : a.ntris - 1);
   if (thi < t0) {
     // tile owners must not decrease; if they did, the build reports an internal
     // error and this tile stays within its own first object
     if (threadIdx.x == 0) atomicOr(&a.ctl->error, kErrInternal);
     thi = t0;
   }
-  const uint32_t s0 = a.start[t0];  // the carried-in owner starts at or before the tile
+  s0 = __builtin_amdgcn_readfirstlane(a.start[t0]);  // the carried-in owner starts at or before the tile
 #pragma unroll
   for (int k = 0; k < K; ++k) s_slot[pad32(k * Block + tid)] = 0;
   __syncthreads();
@@ -399,7 +458,6 @@ GB_DEV uint32_t expand_tile(const ExpandArgs& a, uint32_t tile, uint64_t npairs,
   }
   __syncthreads();
   // inclusive max-scan over the tile's slots, K consecutive slots per thread
-  uint32_t sv[K];
   uint32_t run = 0;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -412,6 +470,21 @@ GB_DEV uint32_t expand_tile(const ExpandArgs& a, uint32_t tile, uint64_t npairs,
     run = run > sv[k] ? run : sv[k];
     sv[k] = run;
   }
+  return n;
+}
+
+// s_slot must hold padded(Block * K) words.  Returns the tile's item count.
+// OneGrid: the caller guarantees that the tile's objects lie in one grid.
+// coords (optional, blocked single-grid tiles only): each item's cell
+// coordinates packed as x | y << 10 | z << 20.
+template <int Block, int K, bool Batched, int Layout = kStriped, bool OneGrid = false>
+GB_DEV uint32_t expand_tile(const ExpandArgs& a, uint32_t tile, uint64_t npairs, uint32_t ntiles, uint32_t* s_slot,
+                            uint32_t* s_wtot, uint32_t (&keys)[K], uint32_t (&vals)[K], uint32_t* coords = nullptr) {
+  constexpr int N = Block * K;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t base = static_cast<uint64_t>(tile) * N;
+  uint32_t sv[K], t0, s0;
+  const uint32_t n = tile_owners<Block, K>(a, tile, npairs, ntiles, s_slot, s_wtot, sv, t0, s0);
   if constexpr (Layout == kStriped) {
 #pragma unroll
     for (int k = 0; k < K; ++k) s_slot[pad32(tid * K + k)] = sv[k];

@@ -36,10 +36,11 @@ struct PlanArgs {
   uint32_t* tfg;
   const uint4* tfo_work;   // ... and the runs of it the count left for this kernel
   uint32_t tfo_work_cap;
+  const uint64_t* grid_pairs;  // record builds: each grid's pair count (else they come from start)
   Control* ctl;
 };
 
-template <int Block, bool Batched>
+template <int Block, bool Batched, bool Rec = false>
 __global__ __launch_bounds__(Block) void plan_kernel(PlanArgs a) {
   __shared__ uint32_t s_wtot[Block / kWave];
   {
@@ -53,13 +54,28 @@ __global__ __launch_bounds__(Block) void plan_kernel(PlanArgs a) {
       }
     }
   }
-  const uint64_t total = a.ctl->npairs;
   const uint32_t G = a.gs.ngrids;
-  if (threadIdx.x == 0 && total > 0xFFFFFFFFull) atomicOr(a.cap_flag, 2u);  // 32-bit pair indices overflow
-  for (uint32_t g = threadIdx.x; g < G; g += Block) {
-    const uint32_t tb = grid_at<Batched>(a.gs, g).tri_base;
-    a.run[g].pair_base = tb < a.ntris ? a.start[tb] : total;
+  uint64_t total;
+  if constexpr (Rec) {
+    // the grids' pair counts, scanned into their first pairs
+    __shared__ uint64_t s_wtot64[Block / kWave];
+    total = 0;
+    for (uint32_t g0 = 0; g0 < G; g0 += Block) {
+      const uint32_t g = g0 + threadIdx.x;
+      uint64_t part;
+      const uint64_t ex = block_exclusive_sum64<Block>(g < G ? a.grid_pairs[g] : 0, s_wtot64, part);
+      if (g < G) a.run[g].pair_base = total + ex;
+      total += part;
+    }
+    if (threadIdx.x == 0) a.ctl->npairs = total;
+  } else {
+    total = a.ctl->npairs;
+    for (uint32_t g = threadIdx.x; g < G; g += Block) {
+      const uint32_t tb = grid_at<Batched>(a.gs, g).tri_base;
+      a.run[g].pair_base = tb < a.ntris ? a.start[tb] : total;
+    }
   }
+  if (threadIdx.x == 0 && total > 0xFFFFFFFFull) atomicOr(a.cap_flag, 2u);  // 32-bit pair indices overflow
   __syncthreads();
   uint32_t carry = 0;
   for (uint32_t g0 = 0; g0 < G; g0 += Block) {

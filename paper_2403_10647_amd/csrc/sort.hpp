@@ -24,7 +24,7 @@ struct SortPassArgs {
   uint64_t* status;         // [ntiles][radix] look-back words (zeroed)
   uint32_t narrow;          // 1: launch the 32-bit look-back word kernel (every pass value below 2^30)
   uint64_t n;               // pairs, when not read from the control block
-  uint32_t n_from_ctl;      // 1: n = ctl->npairs
+  uint32_t n_from_ctl;      // 1: n = ctl->npairs, 2: n = ctl->nitems (record builds)
   uint32_t hist_copies;     // the pass's digit histogram is the sum of this many copies ...
   uint32_t hist_stride;     // ... hist_stride words apart
   uint32_t shift;
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(Block, onesweep_waves(Block, K, RB, Source)) void o
   __shared__ uint32_t s_tile;
 
   if (a.n_from_ctl && build_failed(a.ctl)) return;
-  const uint64_t n = a.n_from_ctl ? a.ctl->npairs : a.n;
+  const uint64_t n = a.n_from_ctl == 0 ? a.n : a.n_from_ctl == 2 ? a.ctl->nitems : a.ctl->npairs;
   const uint32_t ntiles = static_cast<uint32_t>((n + N - 1) / N);
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = lane_id();
