@@ -16,10 +16,11 @@
 // record of the workspace; the culled expansion then tests each box pair
 // against its triangle's record, keeps the survivors in object order (a tile
 // scan plus a decoupled look-back over tiles), and feeds the kept count to the
-// radix sort and the ranges.
+// radix sort and the ranges.  Where boxes are large, the rows of the boxes are
+// tested instead and the build goes on by records.
 #pragma once
 
-#include "ranges.hpp"
+#include "records.hpp"
 
 namespace gb {
 
@@ -328,6 +329,242 @@ __global__ __launch_bounds__(Block, 6) void expand_cull_kernel(CullArgs a) {
   if constexpr (RB > 0) flush_hist<RB, Block>(a.o.plan, a.o.hist, s_hist);
 }
 
+// ---------------------------------------------------------------------------
+// Culled builds by records.  A record is a stretch of one row of a triangle's
+// box, and along a row every axis of the test is one linear function of x: its
+// FP32 value is monotone in x (each operation rounds monotonically), so the
+// cells an axis does not separate are a stretch, and so are the row's kept
+// cells.  Their ends come from each axis' bounds by one division, once as cells
+// that are surely separated beyond and once as cells that are surely not within;
+// where the two differ (an end within rounding of a cell's corner) the test
+// itself moves the ends in until both are kept.  So a row costs one look at
+// seven axes, not one test per cell of the box.
+// ---------------------------------------------------------------------------
+
+// Where below <= c0 * x + r <= above holds along a row, as bounds on x: outside
+// [lo, hi] it surely does not hold, inside [lo_in, hi_in] it surely does (as the
+// test computes it).  The test applies to triangles inside the grid only, so all
+// is finite.  The test's value differs from the real one by at most 5 roundings
+// of a sum of |terms| <= size, and r and the differences below add 5 more, so the
+// bounds are moved by 16 (2^-20 * (size + |bounds|)) either way; the reciprocal
+// and the products are within 2^-22 of their value, which is less than kRowSlack
+// where |x| <= 2048, and where l and d cancel is covered by the 6 roundings to
+// spare (|l| <= d + 1024 there).
+constexpr float kRowSlack = 0.001f;
+
+struct RowBounds {
+  float lo, hi, lo_in, hi_in;
+
+  GB_DEV void narrow(float c0, float size, float above, float below, float r) {
+    const float w = 9.5367431640625e-07f * (size + fabsf(above) + fabsf(below)) + 1e-14f;
+    const float dl = (below - w) - r, dh = (above + w) - r;
+    if (fabsf(c0) < 8.6736173798840355e-19f) {  // 2^-60: 1024 * c0 is below the 1e-14, the same everywhere on the row
+      if (!(dl <= 0.0f && dh >= 0.0f)) lo = 4096.0f;
+      if (!(dl + 2.0f * w <= 0.0f && dh - 2.0f * w >= 0.0f)) lo_in = 4096.0f;
+      return;
+    }
+    const float inv = __builtin_amdgcn_rcpf(c0);
+    const float t0 = dl * inv, t1 = dh * inv, d = 2.0f * w * fabsf(inv);
+    const float l = fminf(t0, t1), h = fmaxf(t0, t1);
+    lo = fmaxf(lo, l);
+    hi = fminf(hi, h);
+    lo_in = fmaxf(lo_in, l + d);
+    hi_in = fminf(hi_in, h - d);
+  }
+};
+
+GB_DEV CullEdge load_edge(const float4* rec, uint32_t obj, int i) {
+  const float4* g = rec + static_cast<uint64_t>(obj) * kRecWords4 + 2 + 3 * i;
+  const float4 g0 = g[0], g1 = g[1], g2 = g[2];
+  CullEdge e;
+  e.c[0][0] = g0.x;
+  e.c[0][1] = g0.y;
+  e.c[1][0] = g0.z;
+  e.c[1][1] = g0.w;
+  e.c[2][0] = g1.x;
+  e.c[2][1] = g1.y;
+  e.above[0] = g1.z;
+  e.above[1] = g1.w;
+  e.above[2] = g2.x;
+  e.below[0] = g2.y;
+  e.below[1] = g2.z;
+  e.below[2] = g2.w;
+  return e;
+}
+
+struct CullRecordsArgs {
+  CullArgs c;               // c.o.cells/objs receive the kept records, at most c.dest_cap
+  SegCode code;             // wy = 0: a segment lies in one row
+};
+
+// The expansion into records with each record narrowed to its kept cells and the
+// empty ones dropped: kept records in object order, their digit histograms, their
+// count (control block: scratch[0]) and their pairs (kept).  A tile's records go
+// through LDS and are looked at one per lane: neighbours are rows of one triangle
+// and read the same record.  Bound by the latency of those reads and of the
+// tile's barriers at 4 waves per SIMD (2 waves: a third slower), so a row's
+// eleven words are loaded together; by a thread's own 4 records with the test at
+// both ends of each 1152 us (1M hairball-like, 446M box pairs), with the ends
+// known from the division 1262, with one load of the words 1185; at 1M uniform
+// 177, 113, 109.  The expansion that tests each box pair takes 3130 us for the
+// first.
+template <int Block, int K, int RB>
+__global__ __launch_bounds__(Block, 4) void cull_rows_kernel(CullRecordsArgs a) {
+  constexpr int N = Block * K;
+  constexpr int R = 1 << RB;
+  static_assert(N <= 65536, "a slot of the tile is held in 16 bits");
+  __shared__ uint32_t s_owner[padded(N)];   // the expansion's slots, then each slot's stretch: first cell | last << 10
+  __shared__ uint32_t s_val[N], s_xyz[N];   // each slot's record and first cell
+  __shared__ uint16_t s_list[N];            // slots whose ends are still to test
+  __shared__ uint32_t s_hist[4 * R];
+  __shared__ uint32_t s_wtot[Block / kWave];
+  __shared__ uint64_t s_prefix, s_pairs;
+  __shared__ uint32_t s_tile, s_n;
+  constexpr uint32_t kStretch = 1u << 31;
+  Control* const ctl = a.c.o.ctl;
+  if (build_failed(ctl)) return;
+  const uint64_t nrec = ctl->nitems;
+  const uint32_t ntiles = static_cast<uint32_t>((nrec + N - 1) / N);
+  clear_status<Block>(a.c.o.clear, nrec);
+  for (uint32_t i = threadIdx.x; i < a.c.o.plan.passes * R; i += Block) s_hist[i] = 0;
+  if (threadIdx.x == 0) s_pairs = 0;
+  const uint32_t tid = threadIdx.x;
+  const float4* const rec = a.c.rec;
+  const uint32_t wx = a.code.wx, kmask = (1u << a.code.ck) - 1u, xmask = (1u << wx) - 1u;
+  const uint32_t omask = (1u << a.code.objbits) - 1u;
+  while (true) {
+    const uint32_t tile = next_tile(&ctl->tile_counter[kCtrExpand], &s_tile);
+    if (tile >= ntiles) break;
+    if (tid == 0) s_n = 0;  // (read after the next barriers)
+    uint32_t keys[K], vals[K], xyz[K];
+    const uint32_t n = record_tile<Block, K, false, true, true>(a.c.o.ex, a.code, tile, nrec, ntiles, s_owner, s_wtot,
+                                                                keys, vals, xyz);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t x = xyz[k] & 1023u;
+      s_owner[tid * K + k] = kStretch | x | ((x + (keys[k] & xmask)) << 10);
+      s_val[tid * K + k] = vals[k];
+      s_xyz[tid * K + k] = xyz[k];
+    }
+    __syncthreads();
+    // the estimates, a record per lane
+    for (uint32_t i = tid; i < (n + kWave - 1) / kWave * kWave; i += Block) {
+      const bool on = i < n;
+      const uint32_t obj = on ? s_val[i] & omask : 0u, row = s_xyz[i], st = s_owner[i];
+      const float4* const r4 = rec + static_cast<uint64_t>(obj) * kRecWords4;
+      const float y = static_cast<float>((row >> 10) & 1023u), z = static_cast<float>(row >> 20);
+      const float4 g0 = r4[0], g1 = r4[1];
+      const bool test = on && __float_as_uint(g1.y) != 0u;
+      bool list = false;
+      if (test) {
+        RowBounds x;
+        x.lo = static_cast<float>(st & 1023u);
+        x.hi = static_cast<float>((st >> 10) & 1023u);
+        x.lo_in = x.lo - 1.0f;  // (no axis moves the record's own ends)
+        x.hi_in = x.hi + 1.0f;
+        x.narrow(g0.x, 1024.0f * (fabsf(g0.x) + fabsf(g0.y) + fabsf(g0.z)), g0.w, g1.x, g0.y * y + g0.z * z);
+        CullEdge d[3];  // (all loads in flight: what bounds this loop is their latency)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) d[e] = load_edge(rec, obj, e);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          // the axis without x is tested as each cell would be
+          const float cx = __fadd_rn(__fmul_rn(d[e].c[0][0], y), __fmul_rn(d[e].c[0][1], z));
+          if ((cx > d[e].above[0]) | (cx < d[e].below[0])) x.lo = 4096.0f;
+          x.narrow(d[e].c[1][0], 1024.0f * (fabsf(d[e].c[1][0]) + fabsf(d[e].c[1][1])), d[e].above[1], d[e].below[1],
+                   d[e].c[1][1] * z);
+          x.narrow(d[e].c[2][0], 1024.0f * (fabsf(d[e].c[2][0]) + fabsf(d[e].c[2][1])), d[e].above[2], d[e].below[2],
+                   d[e].c[2][1] * y);
+        }
+        const float lo = ceilf(x.lo - kRowSlack), hi = floorf(x.hi + kRowSlack);
+        s_owner[i] = lo <= hi ? kStretch | static_cast<uint32_t>(lo) | (static_cast<uint32_t>(hi) << 10) : 0u;
+        list = lo <= hi && !(lo >= x.lo_in + kRowSlack && hi <= x.hi_in - kRowSlack);
+      }
+      const uint64_t lm = ballot(list);
+      uint32_t at = 0;
+      if (lane_id() == 0 && lm) at = atomicAdd(&s_n, static_cast<uint32_t>(__builtin_popcountll(lm)));
+      at = __builtin_amdgcn_readfirstlane(at) + mbcnt(lm);
+      if (list) s_list[at] = static_cast<uint16_t>(i);
+    }
+    __syncthreads();
+    // the ends moved in to kept cells
+    for (uint32_t i = tid; i < s_n; i += Block) {
+      const uint32_t slot = s_list[i], obj = s_val[slot] & omask, row = s_xyz[slot];
+      const float y = static_cast<float>((row >> 10) & 1023u), z = static_cast<float>(row >> 20);
+      const float4 g0 = rec[static_cast<uint64_t>(obj) * kRecWords4];
+      const float nb = rec[static_cast<uint64_t>(obj) * kRecWords4 + 1].x;
+      const float nv[3] = {g0.x, g0.y, g0.z};
+      uint32_t lo = s_owner[slot] & 1023u, hi = (s_owner[slot] >> 10) & 1023u;
+      bool up = true, some = true;  // the low end first, then the high end
+      while (true) {
+        const float x = static_cast<float>(up ? lo : hi);
+        bool sep = normal_separates(nv, g0.w, nb, x, y, z);
+#pragma unroll 1
+        for (int e = 0; e < 3 && !sep; ++e) sep = edge_separates(load_edge(rec, obj, e), x, y, z);
+        if (sep) {
+          if (lo == hi) {
+            some = false;
+            break;
+          }
+          lo += up ? 1u : 0u;
+          hi -= up ? 0u : 1u;
+        } else {
+          if (!up) break;
+          up = false;
+        }
+        if (!up && lo == hi) break;  // the one cell left is kept
+      }
+      s_owner[slot] = some ? kStretch | lo | (hi << 10) : 0u;
+    }
+    __syncthreads();
+    uint32_t keep = 0, pairs = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t st = s_owner[tid * K + k];
+      if (tid * K + k < n && (st & kStretch)) {
+        keep |= 1u << k;
+        const uint32_t lo = st & 1023u, m1 = ((st >> 10) & 1023u) - lo;
+        const uint32_t val = s_val[tid * K + k];
+        const uint32_t code0 = rect_code(a.code, keys[k], val);
+        const uint32_t code = (((code0 >> wx) + lo - (s_xyz[tid * K + k] & 1023u)) << wx) | m1;
+        keys[k] = (keys[k] & ~kmask) | (code & kmask);
+        s_val[tid * K + k] = (val & omask) | ((code >> a.code.ck) << a.code.objbits);
+        pairs += m1 + 1u;
+      }
+    }
+    uint32_t ttot;
+    const uint32_t texcl = block_exclusive_sum<Block>(static_cast<uint32_t>(__builtin_popcount(keep)), s_wtot, ttot);
+    {
+      const uint32_t wp = wave_inclusive(pairs, OpAdd{});  // (a tile's pairs are at most 2^8 * N)
+      if (lane_id() == kWave - 1) add_u64(&s_pairs, wp);
+    }
+    if (tid < kWave) {
+      const uint64_t p = lookback_wave(a.c.status, tile, ttot);
+      if (tid == 0) {
+        s_prefix = p;
+        if (tile == ntiles - 1) ctl->scratch[0] = p + ttot;
+      }
+    }
+    __syncthreads();
+    uint64_t pos = s_prefix + texcl;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if ((keep >> k) & 1u) {
+        if (pos < a.c.dest_cap) {
+          a.c.o.cells[pos] = keys[k];
+          a.c.o.objs[pos] = s_val[tid * K + k];
+        }
+        ++pos;
+      }
+    }
+    hist_runs_kept<K, RB>(a.c.o.plan, keys, keep, s_hist);
+    __syncthreads();  // s_prefix and the tile's LDS are reused by the next tile
+  }
+  if (tid == 0 && s_pairs) add_u64(&ctl->kept, s_pairs);  // one add per workgroup
+  flush_hist<RB, Block>(a.c.o.plan, a.c.o.hist, s_hist);
+}
+
 // After the culled expansion: the kept count becomes the build's pair count
 // (the box count is kept beside it), the capacity is checked against it, and
 // the one grid's range plan is sized for it.
@@ -337,6 +574,7 @@ struct CullCommitArgs {
   uint64_t out_cap;
   uint64_t ncells;
   uint32_t merge_tile;
+  uint32_t records;         // 1: a build by records, whose kept records are counted beside its pairs
 };
 
 __global__ void cull_commit_kernel(CullCommitArgs a) {
@@ -351,6 +589,7 @@ __global__ void cull_commit_kernel(CullCommitArgs a) {
   }
   c->box_npairs = box;
   c->npairs = kept;
+  if (a.records) c->nitems = c->nitems == 0 ? 0 : c->scratch[0];
   if (kept > a.out_cap) c->cap_flag |= 1u;
   a.run[0].npairs = kept;
   const uint32_t mt = static_cast<uint32_t>((a.ncells + 1 + kept + a.merge_tile - 1) / a.merge_tile);

@@ -289,9 +289,10 @@ constexpr uint64_t kSegPairs = 384, kSegPairsDense = 768, kSegPairsFew = 48, kFe
 
 // Segments for grids of `cells` cells in all (rx, ry: the widest grid's) and
 // about `pairs` pairs: 2^(wx + wy) cells each, whole rows while rows are short.
-// (wider: twice as wide, that many times.)  False when a record would not fit its 64 bits
+// (wider: twice as wide, that many times;
+// rows: no segment holds more than one row.)  False when a record would not fit its 64 bits
 // (or a list entry its scan word), or there is nothing wider.
-bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pairs, uint32_t wider, RecordPlan* rp) {
+bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pairs, uint32_t wider, bool rows, RecordPlan* rp) {
   uint32_t rx = 1, ry = 1, tmax = 1;
   for (uint32_t g = 0; g < ngrids; ++g) {
     rx = std::max(rx, grids[g].res[0]);
@@ -312,7 +313,7 @@ bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pair
   if ((wb += wider) > 8) return false;
   SegCode c{};
   c.wx = std::min(wb, bits_for(rx));
-  c.wy = std::min(wb - c.wx, bits_for(ry));
+  c.wy = rows ? 0u : std::min(wb - c.wx, bits_for(ry));
   uint64_t nsegs = 0;
   for (uint32_t g = 0; g < ngrids; ++g) {
     set_segments(grids[g], c.wx, c.wy);
@@ -334,7 +335,8 @@ bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pair
 // Workspace of a build by records.  It takes no more than make_layout's for the
 // same build except for its list of segments, so a build runs by records where
 // that fits what the caller was asked for.
-Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& rp, uint32_t ngrids, bool batched) {
+Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& rp, uint32_t ngrids, bool batched,
+                          bool culled) {
   Layout L{};
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -352,12 +354,14 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.count_status = take(std::max<size_t>(L.ncount_tiles, 1) * 8);
   L.grid_pairs = take(static_cast<size_t>(ngrids) * 8);
   L.list_status = take((ceil_div(cap_pairs, kSegListTile) + 1) * 8);
+  L.cull_status = take(culled ? static_cast<size_t>(L.ntfo) * 8 : 0);
   L.zero_end = o;
   L.start = take(ntris * 4);
   L.box = take(ntris * 8);
   L.tfo = take(static_cast<size_t>(L.ntfo) * 4);
   L.tfg = take(batched ? static_cast<size_t>(L.ntfo) * 4 : 0);
   L.tfo_work = take(tfo_work_cap(L.ntfo) * sizeof(uint4));
+  L.cull_rec = take(culled ? ntris * sizeof(CullRecord) : 0);
   L.sort_status = take(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
                        (narrow_words(cap_pairs) ? 4 : 8));
   L.keys_alt = take(cap_pairs * 4);
@@ -462,15 +466,29 @@ bool records_allowed() { return g_build_path == 0 && !g_fused_expand && !g_per_o
 constexpr uint64_t kRecordsFew = uint64_t{1} << 18;
 bool records_pay(uint64_t pairs, uint64_t ntris) { return pairs <= kRecordsFew || 4 * pairs >= 13 * ntris; }
 
+// A culled build's records are rows of the boxes, each tested once per axis, so
+// what they save grows with the boxes.  Box pairs per triangle -> the build by
+// tested pairs against this one, us: 1.3 (100k arch-like) 129 / 160, 2.1 (1M) 226
+// / 244, 2.5 (100k uniform) 135 / 127, 3.0 (3M arch-like) 584 / 543, 5.4 (10M)
+// 2169 / 1776, 30 (1M mixed) 586 / 359, 446 (1M hairball-like) 3590 / 1600.  Small
+// builds are launches: below 2^20 box pairs this path's own 6 us (8k to 30k
+// hairball-like: 104 / 111, 115 / 126) pay only where a radix pass falls away (2k:
+// 98 / 88); at 1.4M box pairs (300k mixed) 165 / 147.
+constexpr uint64_t kCullRecordsFew = uint64_t{1} << 20;
+bool cull_records_pay(uint64_t box_pairs, uint64_t ntris, int pair_passes, int record_passes) {
+  return 5 * box_pairs >= 12 * ntris && (box_pairs >= kCullRecordsFew || record_passes < pair_passes);
+}
+
 // Makes b a build by records when its grids, about `pairs` pairs, allow it and the workspace holds it.
 void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t cap, uint64_t pairs, size_t ws_bytes) {
-  if (b.ntris == 0 || cap == 0 || !records_pay(pairs, b.ntris)) return;
+  if (b.ntris == 0 || cap == 0 || (!b.culled && !records_pay(pairs, b.ntris))) return;
   RecordPlan rp{};
   Layout L{};
   // a workspace too small for the list of segments: wider segments, fewer of them
   for (uint32_t wider = 0;; ++wider) {
-    if (!plan_records(grids, ngrids, cells, pairs, wider, &rp)) return;
-    L = make_record_layout(b.ntris, cap, rp, ngrids, b.batched);
+    if (!plan_records(grids, ngrids, cells, pairs, wider, b.culled, &rp)) return;
+    if (b.culled && !cull_records_pay(cap, b.ntris, b.plan.sp.passes, rp.plan.sp.passes)) return;
+    L = make_record_layout(b.ntris, cap, rp, ngrids, b.batched, b.culled);
     if (L.total <= ws_bytes) break;
   }
   b.rec = true;
@@ -711,6 +729,36 @@ int choose_path(uint64_t npairs, uint64_t ncells) {
   return npairs <= kCompactMaxPairs && static_cast<double>(npairs) <= kCompactMaxPairsPerCell * ncells ? 1 : 0;
 }
 
+// Each triangle's overlap test, one thread per triangle.
+int launch_cull_records(Build& b) {
+  CullRecordArgs r{};
+  r.grid = b.gs.one;
+  r.box = at<uint64_t>(b.ws, b.L.box);
+  r.rec = at<CullRecord>(b.ws, b.L.cull_rec);
+  r.ntris = b.ntris;
+  r.ctl = at<Control>(b.ws, b.L.ctl);
+  if (b.ntris == 0) return GRID_OK;
+  TraceScope tr(b.s, "cull_record");
+  cull_record_kernel<256><<<static_cast<uint32_t>(std::min<uint64_t>(ceil_div(b.ntris, 256), 8192)), 256, 0, b.s>>>(r);
+  GB_LAUNCHED();
+  return GRID_OK;
+}
+
+// The kept pairs (and records) made the build's, checked against the outputs.
+int launch_cull_commit(Build& b) {
+  CullCommitArgs c{};
+  c.ctl = at<Control>(b.ws, b.L.ctl);
+  c.run = at<GridRun>(b.ws, b.L.run);
+  c.out_cap = b.out_cap;
+  c.ncells = ncells_of(b.gs.one.res);
+  c.merge_tile = kMergeTile;
+  c.records = b.rec ? 1u : 0u;
+  TraceScope ts(b.s, "cull_commit");
+  cull_commit_kernel<<<1, kWave, 0, b.s>>>(c);
+  GB_LAUNCHED();
+  return GRID_OK;
+}
+
 // Culled builds: the expansion that tests every box pair and keeps the pairs
 // whose triangle touches the cell (into cells/objs, at most dest_cap of them),
 // then the kept count made the build's pair count.
@@ -718,20 +766,10 @@ template <int RB>
 int launch_cull(Build& b, uint32_t* cells, uint32_t* objs, uint64_t dest_cap, uint64_t box_cap) {
   if (box_cap > 0) {
     if (!cells || !objs) return GRID_E_INVAL;
-    CullRecordArgs r{};
-    r.grid = b.gs.one;
-    r.box = at<uint64_t>(b.ws, b.L.box);
-    r.rec = at<CullRecord>(b.ws, b.L.cull_rec);
-    r.ntris = b.ntris;
-    r.ctl = at<Control>(b.ws, b.L.ctl);
-    if (b.ntris > 0) {
-      TraceScope tr(b.s, "cull_record");
-      cull_record_kernel<256><<<static_cast<uint32_t>(std::min<uint64_t>(ceil_div(b.ntris, 256), 8192)), 256, 0,
-                                b.s>>>(r);
-      GB_LAUNCHED();
-    }
+    int st = launch_cull_records(b);
+    if (st) return st;
     CullArgs a{};
-    a.rec = reinterpret_cast<const float4*>(r.rec);
+    a.rec = at<float4>(b.ws, b.L.cull_rec);
     a.o.ex = expand_args(b);
     a.o.cells = cells;
     a.o.objs = objs;
@@ -746,16 +784,7 @@ int launch_cull(Build& b, uint32_t* cells, uint32_t* objs, uint64_t dest_cap, ui
     kern<<<resident_blocks(kern, kExpandBlock, ceil_div(box_cap, kExpandTile)), kExpandBlock, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
-  CullCommitArgs c{};
-  c.ctl = at<Control>(b.ws, b.L.ctl);
-  c.run = at<GridRun>(b.ws, b.L.run);
-  c.out_cap = b.out_cap;
-  c.ncells = ncells_of(b.gs.one.res);
-  c.merge_tile = kMergeTile;
-  TraceScope ts(b.s, "cull_commit");
-  cull_commit_kernel<<<1, kWave, 0, b.s>>>(c);
-  GB_LAUNCHED();
-  return GRID_OK;
+  return launch_cull_commit(b);
 }
 
 // Each pass runs the kernel built for its own digit width (8..11 bits), so an
@@ -957,6 +986,28 @@ int launch_sort(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t npai
   }
 }
 
+// Culled builds by records: the records narrowed to their kept cells, at most
+// dest_cap of them stored (a kept record holds a pair, so more than that is a
+// capacity error, which the commit raises before any pass runs).
+template <int RB>
+int launch_cull_rows(Build& b, const RecordArgs& ra, uint64_t dest_cap, uint64_t box_cap) {
+  int st = launch_cull_records(b);
+  if (st) return st;
+  CullRecordsArgs a{};
+  a.c.o = ra.o;
+  a.c.rec = at<float4>(b.ws, b.L.cull_rec);
+  a.c.dest_cap = dest_cap;
+  a.c.status = at<uint64_t>(b.ws, b.L.cull_status);
+  a.code = ra.code;
+  {
+    TraceScope ts(b.s, "cull_rows");
+    auto kern = cull_rows_kernel<kRecordBlock, kRecordK, RB>;
+    kern<<<resident_blocks(kern, kRecordBlock, ceil_div(box_cap, kExpandTile)), kRecordBlock, 0, b.s>>>(a);
+    GB_LAUNCHED();
+  }
+  return launch_cull_commit(b);
+}
+
 // A build by records, after its count and plan: records, radix passes over
 // their segments, the list of segments, and each segment's pairs and ranges.
 // Writer i of the sequence (i = -1: the records, then the passes) alternates
@@ -986,7 +1037,10 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
     a.o.ctl = ctl;
     a.code = b.code;
     a.run = at<GridRun>(b.ws, b.L.run);
-    {
+    if (!B && b.culled) {
+      int st = launch_cull_rows<RB>(b, a, P % 2 ? b.out_cap : npairs, npairs);
+      if (st) return st;
+    } else {
       TraceScope ts(b.s, "records");
       auto kern = record_kernel<kRecordBlock, kRecordK, RB, B>;
       kern<<<resident_blocks(kern, kRecordBlock, ceil_div(npairs, kExpandTile)), kRecordBlock, 0, b.s>>>(a);
@@ -1330,18 +1384,22 @@ int grid_build_culled(const float* verts_soa, uint32_t nverts, const uint32_t* t
   if (st) return st;
   b.culled = true;
   b.out_cap = out->cap_pairs;
+  if (records_allowed() && out->cap_pairs > 0)
+    try_records(b, &b.gs.one, 1, ncells_of(res), box_cap, std::min(box_cap, out->cap_pairs), ws_bytes);
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
   b.gs.one.out_ranges = out->ranges;
   if ((st = launch_zero(b.ws, b.L.zero_end, b.s))) return st;
   if ((st = launch_count<false>(b))) return st;
   if ((st = launch_plan<false>(b))) return st;  // checks the box pairs against box_cap
-  if (b.plan.sp.passes == 0 || box_cap == 0) {
+  if (b.rec) {
+    if ((st = launch_records<false>(b, out->cells, out->objs, box_cap))) return st;
+  } else if (b.plan.sp.passes == 0 || box_cap == 0) {
     if ((st = launch_cull<0>(b, out->cells, out->objs, out->cap_pairs, box_cap))) return st;
   } else {
     if ((st = launch_sort<false>(b, out->cells, out->objs, box_cap))) return st;
   }
-  if ((st = launch_ranges<false>(b, ncells_of(res) + 1 + std::min(box_cap, out->cap_pairs)))) return st;
+  if (!b.rec && (st = launch_ranges<false>(b, ncells_of(res) + 1 + std::min(box_cap, out->cap_pairs)))) return st;
   HostCtl h{};
   if ((st = read_ctl(b, &h))) return st;
   if (h.error) return device_error(h.error);

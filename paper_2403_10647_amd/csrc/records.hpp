@@ -53,10 +53,12 @@ GB_DEV SegParams seg_params(const GridDev& G) {
 }
 
 // Records tile * N .. of one expansion tile (N = Block * K), K consecutive
-// ones per thread: keys and values.  Returns the tile's record count.
-template <int Block, int K, bool Batched, bool OneGrid>
+// ones per thread: keys and values.  Returns the tile's record count.  Where
+// (wy = 0): also each record's first cell in the grid, x | y << 10 | z << 20.
+template <int Block, int K, bool Batched, bool OneGrid, bool Where = false>
 GB_DEV uint32_t record_tile(const ExpandArgs& a, const SegCode& c, uint32_t tile, uint64_t nrec, uint32_t ntiles,
-                            uint32_t* s_slot, uint32_t* s_wtot, uint32_t (&keys)[K], uint32_t (&vals)[K]) {
+                            uint32_t* s_slot, uint32_t* s_wtot, uint32_t (&keys)[K], uint32_t (&vals)[K],
+                            uint32_t* xyz = nullptr) {
   constexpr int N = Block * K;
   const uint32_t tid = threadIdx.x;
   const uint64_t base = static_cast<uint64_t>(tile) * N;
@@ -121,6 +123,7 @@ GB_DEV uint32_t record_tile(const ExpandArgs& a, const SegCode& c, uint32_t tile
     const uint32_t code = (((y0 << c.wx) | x0) << (c.wx + c.wy)) | ((y1 - y0) << c.wx) | (x1 - x0);
     keys[k] = (seg << c.ck) | (code & kmask);
     vals[k] = (obj - (Batched ? p.tri_base : 0u)) | ((code >> c.ck) << c.objbits);
+    if constexpr (Where) xyz[k] = (ox + x0) | ((sly + y) << 10) | ((b.lo[2] + z) << 20);  // (one row: sly + y is y)
     if (idx >= n) {
       keys[k] = 0xFFFFFFFFu;
       vals[k] = 0;

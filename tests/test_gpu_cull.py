@@ -138,3 +138,54 @@ def test_culled_capacity_errors(G):
     assert st == G.GRID_E_CAPACITY and nb.value == nbox and o.npairs == 0
     # and then the build with room for everything is exact
     _check(G, s)
+
+
+def _axis_cases(rng, n, res):
+    """Triangles whose rows meet the test's axes in every way: slivers, edges along the grid axes (an
+    axis constant along x), vertices on cell corners (bounds met exactly), slopes of a few millionths,
+    single cells, and vertices outside the grid."""
+    r = np.asarray(res, np.float64)
+    a = rng.uniform(0, 1, (n, 3)) * r
+    b = rng.uniform(0, 1, (n, 3)) * r
+    c = a + (b - a) * rng.uniform(0.3, 0.9, (n, 1)) + rng.normal(0, 0.05, (n, 3))
+    kind = rng.integers(0, 6, n)
+    k = kind == 1
+    b[k, 1:] = a[k, 1:]                       # an edge along x
+    k = kind == 2
+    a[k], b[k], c[k] = np.round(a[k]), np.round(b[k]), np.round(rng.uniform(0, 1, (k.sum(), 3)) * r)
+    k = kind == 3
+    b[k, 1:] = a[k, 1:] + rng.normal(0, 1e-5, (k.sum(), 2))
+    c[k] = a[k] + rng.normal(0, 1e-5, (k.sum(), 3)) + (b[k] - a[k]) * 0.5
+    k = kind == 4
+    b[k], c[k] = a[k] + 0.1, a[k] + np.array([0.1, 0.0, 0.05])
+    v = np.clip(np.stack([a, b, c], 1), 0, r)
+    v[(kind == 5) & (np.arange(n) % 16 == 0), 2, 0] = r[0] + 3.0
+    return v
+
+
+@pytest.mark.parametrize("res,n", [((96, 96, 96), 300), ((1024, 16, 8), 2001), ((1000, 3, 60), 1200),
+                                   ((256, 256, 1), 3000), ((7, 300, 40), 3000)])
+def test_culled_by_records(G, res, n):
+    verts, tris = scenes.soup_from_vertices(_axis_cases(np.random.default_rng(sum(res)), n, res))
+    s = _scene(verts, tris, [0, 0, 0], res, res, name="axes")
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        _, nbox = _check(G, s)
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+    assert nbox >= 1 << 20
+    assert "cull_rows" in k, sorted(k)
+
+
+def test_culled_short_boxes_test_pairs(G):
+    s = scenes.make_scene("arch", seed=3, ntris=30_000)
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        _, nbox = _check(G, s)
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+    assert 5 * nbox < 12 * s.ntris and "cull_rows" not in k, (nbox, sorted(k))
