@@ -2104,7 +2104,7 @@ int grid_raycast(const float* verts_soa, uint32_t nverts, const uint32_t* tris, 
   a.hit_obj = hit_obj;
   hipStream_t s = static_cast<hipStream_t>(stream);
   TraceScope ts(s, "raycast");
-  raycast_kernel<256><<<static_cast<uint32_t>(ceil_div(nrays, 256)), 256, 0, s>>>(a);
+  raycast_kernel<<<static_cast<uint32_t>(ceil_div(nrays, kWave)), kWave, 0, s>>>(a);
   GB_LAUNCHED();
   return GRID_OK;
 }

@@ -100,3 +100,28 @@ def test_raycast_empty_and_axis_rays(G):
     re = G.build(ge)
     ht, ho = G.raycast(ge, re, torch.from_numpy(rays).cuda())
     assert torch.isinf(ht).all() and (ho == -1).all()
+
+
+@pytest.mark.parametrize("nrays,n,res", [(1, 1, (1, 1, 1)), (63, 4095, (1, 1, 1)), (64, 4097, (1, 1, 1)), (65, 9001, (2, 1, 1)),
+                                         (257, 300, (3, 3, 3)), (200, 64, (700, 2, 1))])
+def test_raycast_turns(G, nrays, n, res):
+    """Waves of rays at their edges, cells with more objects than a turn tests at once, long empty walks,
+    equal hits (each triangle three times) and rays that start in a triangle's plane, t = 0 of either sign."""
+    rng = np.random.default_rng(n)
+    a = rng.uniform(0, 1, (n, 1, 3))
+    a[: n // 4, :, 2] = 0.5
+    v = np.clip(a + rng.uniform(-0.2, 0.2, (n, 3, 3)), 0, 1)
+    v[: n // 4, :, 2] = 0.5
+    verts, tris = scenes.soup_from_vertices(np.concatenate([v, v[::-1], v]))
+    s = scenes.Scene("turns", verts, tris, np.zeros(3, np.float32), np.ones(3, np.float32), np.asarray(res, np.uint32))
+    o = rng.uniform(0, 1, (nrays, 3))
+    o[::2, 2] = 0.5
+    d = rng.normal(0, 1, (nrays, 3))
+    d[1::8] = [1.0, 0.0, 0.0]
+    rays = np.ascontiguousarray(np.concatenate([o.T, d.T]).astype(np.float32))
+    _say("raycast turns", nrays, 3 * n, res)
+    g = G.GridInput.from_scene(s)
+    ht, ho = G.raycast(g, G.build(g), torch.from_numpy(rays).cuda())
+    ot, oo = oracle.raycast(s.verts, s.tris, s.lo, s.hi, rays, float("inf"))
+    assert np.array_equal(ho.cpu().numpy().view(np.uint32), oo)
+    assert np.array_equal(ht.cpu().numpy().view(np.uint32), ot.view(np.uint32))
