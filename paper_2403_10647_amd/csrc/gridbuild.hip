@@ -28,7 +28,7 @@ constexpr int kCountBlock = 1024, kCountK = 8;          // 8192 triangles per co
 constexpr int kExpandBlock = 512, kExpandK = 8;         // 4096 pairs per expansion tile
 constexpr int kExpandTile = kExpandBlock * kExpandK;
 constexpr int kExpandTileShift = 12;                    // tfo/tfg hold one entry per expansion tile
-constexpr int kSortBlock = 512, kSortK = 16;            // radix tile shape 0 and the standalone sort: 8192 pairs
+constexpr int kSortBlock = 512, kSortK = 16;            // radix tile shape 0: 8192 pairs
 constexpr int kSortTile = kSortBlock * kSortK;
 constexpr int kSortTileMin = 4096;                      // smallest tile of any radix-pass or expansion shape
 constexpr int kRangesBlock = 256, kRangesK = 16;        // 4096 merge items per range tile
@@ -1711,6 +1711,13 @@ int grid_build_batched(grid_desc* grids, uint32_t ngrids, void* ws, size_t ws_by
 // ---------------------------------------------------------------------------------
 namespace {
 
+// The sort's tiles: 16384 pairs where there are enough of them for every CU, as in
+// a build, else 8192 (16M pairs, three passes: 246 against 279 us; at 4.2M, one
+// pass, 76 and 83 us for the whole sort).
+int sort_arrays_shape(uint64_t n) { return ceil_div(n, sort_shape_tile(3)) >= static_cast<uint64_t>(device_cus()) ? 3 : 0; }
+
+constexpr int kHistBlock = 1024, kHistK = 8;
+
 struct SortLayout {
   size_t ctl, hist, status, total;
   uint32_t ntiles;
@@ -1737,23 +1744,31 @@ int sort_arrays_rb(uint32_t* keys, uint32_t* vals, uint32_t* ka, uint32_t* va, u
                    void* ws, const SortLayout& L, hipStream_t s) {
   Control* ctl = at<Control>(ws, L.ctl);
   const uint64_t stride = static_cast<uint64_t>(L.ntiles) * (1u << RB);
+  const bool narrow = narrow_words(n);
+  const int shape = sort_arrays_shape(n);
+  const uint32_t ntiles = static_cast<uint32_t>(ceil_div(n, sort_shape_tile(shape)));
+  const bool copied = plan.sp.passes % 2 != 0;
   {
     HistArrayArgs h{};
     h.keys = keys;
+    h.vals = vals;
+    h.keys_out = copied ? ka : nullptr;
+    h.vals_out = copied ? va : nullptr;
     h.n = n;
     h.plan = plan.sp;
     h.hist = at<uint32_t>(ws, L.hist);
     h.sort_status = at<uint64_t>(ws, L.status);
     h.status_stride = stride;
-    h.ctl = ctl;
+    h.status_words = (static_cast<uint64_t>(ntiles) << RB) / (narrow ? 2 : 1);
     TraceScope ts(s, "hist_array");
-    hist_array_kernel<kSortBlock, kSortK, RB><<<persistent_blocks(L.ntiles, 3), kSortBlock, 0, s>>>(h);
+    hist_array_kernel<kHistBlock, kHistK, RB>
+        <<<persistent_blocks(ceil_div(n, kHistBlock * kHistK), 1), kHistBlock, 0, s>>>(h);
     GB_LAUNCHED();
   }
-  uint32_t* src_k = keys;
-  uint32_t* src_v = vals;
-  uint32_t* dst_k = ka;
-  uint32_t* dst_v = va;
+  uint32_t* src_k = copied ? ka : keys;
+  uint32_t* src_v = copied ? va : vals;
+  uint32_t* dst_k = copied ? keys : ka;
+  uint32_t* dst_v = copied ? vals : va;
   for (uint32_t p = 0; p < plan.sp.passes; ++p) {
     SortPassArgs a{};
     a.keys_in = src_k;
@@ -1765,26 +1780,17 @@ int sort_arrays_rb(uint32_t* keys, uint32_t* vals, uint32_t* ka, uint32_t* va, u
     a.hist_stride = 0;
     a.status = at<uint64_t>(ws, L.status) + p * stride;
     a.n = n;
-    a.narrow = narrow_words(n);
+    a.narrow = narrow;
     a.n_from_ctl = 0;
     a.shift = plan.sp.shift[p];
     a.width = plan.sp.width[p];
     a.counter = kCtrSort0 + p;
     a.ctl = ctl;
     TraceScope ts(s, "onesweep");
-    if (a.narrow)
-      onesweep_kernel<kSortBlock, kSortK, RB, kFromArrays, kToArrays, false, true>
-          <<<persistent_blocks(L.ntiles, 2), kSortBlock, 0, s>>>(a);
-    else
-      onesweep_kernel<kSortBlock, kSortK, RB, kFromArrays, kToArrays, false, false>
-          <<<persistent_blocks(L.ntiles, 2), kSortBlock, 0, s>>>(a);
-    GB_LAUNCHED();
+    int st = launch_pass<false>(a, pass_bits(a.width), false, false, ntiles, s, shape);
+    if (st) return st;
     std::swap(src_k, dst_k);
     std::swap(src_v, dst_v);
-  }
-  if (src_k != keys) {
-    GB_TRY(hipMemcpyAsync(keys, src_k, n * 4, hipMemcpyDeviceToDevice, s));
-    GB_TRY(hipMemcpyAsync(vals, src_v, n * 4, hipMemcpyDeviceToDevice, s));
   }
   return GRID_OK;
 }

@@ -298,48 +298,70 @@ __global__ __launch_bounds__(Block, onesweep_waves(Block, K, RB, Source)) void o
   }
 }
 
-// Digit histograms of every pass from keys held in an array (one read).
+// Digit histograms of every pass from keys held in an array (one read), and, for
+// an odd number of passes, the pairs copied to where the first pass reads them,
+// so that the last one ends in the caller's arrays.  Bound by HBM when it copies
+// (16M pairs: 50 us, 5.1 TB/s; copying after the last pass took 60 us more), and
+// otherwise by its loads and the workgroups' adds to the same global counters,
+// which is why there is one workgroup a CU: 18 us, 21 with two, 30 with four of
+// 512 threads; 46 with keys loaded one by one in tiles taken from a counter.
 struct HistArrayArgs {
   const uint32_t* keys;
+  const uint32_t* vals;
+  uint32_t* keys_out;       // copies of the pairs, or null
+  uint32_t* vals_out;
   uint64_t n;
   SortPlan plan;
   uint32_t* hist;           // [4][kRadixMax]
-  uint64_t* sort_status;    // [passes][status_stride], cleared here
-  uint64_t status_stride;
-  Control* ctl;
+  uint64_t* sort_status;    // [passes][status_stride], of which the first status_words are cleared here
+  uint64_t status_stride, status_words;
 };
 
 template <int Block, int K, int RB>
 __global__ __launch_bounds__(Block) void hist_array_kernel(HistArrayArgs a) {
-  constexpr int N = Block * K;
+  constexpr uint32_t N = Block * K;
   constexpr int R = 1 << RB;
   __shared__ uint32_t s_hist[4 * R];
-  __shared__ uint32_t s_tile;
-  const uint32_t ntiles = static_cast<uint32_t>((a.n + N - 1) / N);
-  {
-    const uint64_t per_pass = static_cast<uint64_t>(ntiles) * R;
-    const uint64_t nwords = static_cast<uint64_t>(a.plan.passes) * per_pass;
-    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * Block + threadIdx.x; i < nwords;
+  const uint32_t tid = threadIdx.x;
+  for (uint32_t p = 0; p < a.plan.passes; ++p)
+    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * Block + tid; i < a.status_words;
          i += static_cast<uint64_t>(gridDim.x) * Block)
-      a.sort_status[(i / per_pass) * a.status_stride + i % per_pass] = 0;
-  }
-  for (int i = threadIdx.x; i < 4 * R; i += Block) s_hist[i] = 0;
+      a.sort_status[p * a.status_stride + i] = 0;
+  for (uint32_t i = tid; i < 4 * R; i += Block) s_hist[i] = 0;
   __syncthreads();
-  while (true) {
-    const uint32_t tile = next_tile(&a.ctl->tile_counter[kCtrHist], &s_tile);
-    if (tile >= ntiles) break;
-    const uint64_t base = static_cast<uint64_t>(tile) * N;
+  for (uint64_t base = static_cast<uint64_t>(blockIdx.x) * N; base < a.n; base += static_cast<uint64_t>(gridDim.x) * N) {
+    const uint32_t nt = static_cast<uint32_t>(a.n - base < N ? a.n - base : N);
+    uint32_t key[K];
+#pragma unroll
     for (int k = 0; k < K; ++k) {
-      const uint64_t i = base + static_cast<uint64_t>(k) * Block + threadIdx.x;
-      if (i < a.n) {
-        const uint32_t key = a.keys[i];
-        for (uint32_t p = 0; p < a.plan.passes; ++p)
-          atomicAdd(&s_hist[p * R + ((key >> a.plan.shift[p]) & ((1u << a.plan.width[p]) - 1u))], 1u);
+      const uint32_t i = k * Block + tid;
+      key[k] = a.keys[base + (i < nt ? i : nt - 1)];
+    }
+    if (a.keys_out) {
+      uint32_t val[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint32_t i = k * Block + tid;
+        val[k] = a.vals[base + (i < nt ? i : nt - 1)];
       }
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const uint32_t i = k * Block + tid;
+        if (i < nt) {
+          a.keys_out[base + i] = key[k];
+          a.vals_out[base + i] = val[k];
+        }
+      }
+    }
+    for (uint32_t p = 0; p < a.plan.passes; ++p) {
+      const uint32_t shift = a.plan.shift[p], mask = (1u << a.plan.width[p]) - 1u;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (k * Block + tid < nt) atomicAdd(&s_hist[p * R + ((key[k] >> shift) & mask)], 1u);
     }
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < a.plan.passes * R; i += Block) {
+  for (uint32_t i = tid; i < a.plan.passes * R; i += Block) {
     const uint32_t v = s_hist[i];
     if (v) atomicAdd(&a.hist[(i / R) * kRadixMax + (i % R)], v);
   }
