@@ -169,8 +169,8 @@ int g_sort_shape = 3;  // radix passes from arrays: 0 = 512 x 16, 1 = 256 x 16, 
                        // 4 = 1024 x 15
 
 int sort_shape_tile(int shape) { return shape == 1 ? 4096 : shape == 3 ? 16384 : shape == 4 ? 15360 : 8192; }
-// 1: a build whose pairs would fill fewer 16384-pair tiles than the GPU has
-// CUs runs its passes from arrays in 256 x 16 tiles, whatever sort_shape says.
+// 1: a build of too few pairs for the knob's tiles runs its passes from arrays
+// in the shape pass_shape gives, whatever sort_shape says.
 int g_small_tiles = 1;
 
 Plan make_plan(uint32_t bits, int max_digit = -1) {
@@ -594,14 +594,26 @@ uint32_t pass_tile(const Build& b, uint32_t p) {
                                          : static_cast<uint32_t>(sort_shape_tile(b.sort_shape));
 }
 
-// Radix tile shape for a build of at most cap_pairs pairs: the sort_shape
-// knob's, unless the pairs would fill fewer 16384-pair tiles than the GPU has
-// CUs.  Each tile's phases take about the same time whatever its size, so a
-// build with few tiles finishes sooner with more, smaller tiles spread over
-// more CUs (a 17K-pair pass: 15 against 20 us).
-int build_sort_shape(uint64_t cap_pairs) {
-  if (g_small_tiles && ceil_div(cap_pairs, 16384) < static_cast<uint64_t>(device_cus())) return 1;
-  return g_sort_shape;
+// Radix tile shape for passes over n items.  A tile's phases take about the same
+// time whatever its size, and a CU holds one 1024 x 16 tile, so that shape is
+// best where the tiles fill the CUs once and where there are many rounds; fewer
+// items finish sooner in smaller tiles on more CUs, and a few more than one round
+// holds in tiles of which a CU holds two.  Whole builds, us, 256 x 16 / 512 x 16
+// / 1024 x 8 / 1024 x 16: 17K pairs 74.6 74.5 73.2 77.5, 490K 131 131 128 137,
+// 1.4M 142 135 131 140, 2.1M 161 147 144 152; 2.9M 183 164 172 162, 3.9M 209 182
+// 189 174; 4.3M 221 194 199 202, 5.3M 260 233 239 242; 8.7M 378 323 343 324, 14.9M
+// 580 494 522 480.  (estimate: n is an estimate, so the band beyond one round is not
+// taken: 12.3M pairs, estimated 6.2M, 182 and 178.)
+int pass_shape(uint64_t n, bool estimate) {
+  const uint64_t tiles = ceil_div(n, sort_shape_tile(3)), cus = static_cast<uint64_t>(device_cus());
+  if (16 * tiles < 9 * cus) return 2;
+  return !estimate && tiles > cus && 2 * tiles <= 3 * cus ? 0 : 3;
+}
+
+// The sort_shape knob's, where pass_shape would take its default.
+int build_sort_shape(uint64_t n, bool estimate) {
+  const int shape = g_small_tiles ? pass_shape(n, estimate) : 3;
+  return shape == 3 ? g_sort_shape : shape;
 }
 
 // The look-back words each radix pass of b's plan will use (kernels built for
@@ -896,7 +908,7 @@ int launch_sort_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t n
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
   const bool fused = fused_first_pass(b);
-  b.sort_shape = build_sort_shape(npairs);  // before anything sizes or clears the passes' look-back words
+  b.sort_shape = build_sort_shape(npairs, false);  // before anything sizes or clears the passes' look-back words
   const uint32_t* in_k = nullptr;
   const uint32_t* in_v = nullptr;
   if (fused) {
@@ -1018,7 +1030,7 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
   const SortPlan& sp = b.plan.sp;
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
-  b.sort_shape = build_sort_shape(npairs / 2);
+  b.sort_shape = build_sort_shape((b.culled ? std::min(npairs, b.out_cap) : npairs) / 2, true);
   b.rec_cap = npairs;
   const Dest bufs[2] = {{at<uint32_t>(b.ws, b.L.keys_alt), at<uint32_t>(b.ws, b.L.vals_alt)},
                         B ? Dest{at<uint32_t>(b.ws, b.L.keys_alt2), at<uint32_t>(b.ws, b.L.vals_alt2)}
@@ -1711,11 +1723,6 @@ int grid_build_batched(grid_desc* grids, uint32_t ngrids, void* ws, size_t ws_by
 // ---------------------------------------------------------------------------------
 namespace {
 
-// The sort's tiles: 16384 pairs where there are enough of them for every CU, as in
-// a build, else 8192 (16M pairs, three passes: 246 against 279 us; at 4.2M, one
-// pass, 76 and 83 us for the whole sort).
-int sort_arrays_shape(uint64_t n) { return ceil_div(n, sort_shape_tile(3)) >= static_cast<uint64_t>(device_cus()) ? 3 : 0; }
-
 constexpr int kHistBlock = 1024, kHistK = 8;
 
 struct SortLayout {
@@ -1745,7 +1752,7 @@ int sort_arrays_rb(uint32_t* keys, uint32_t* vals, uint32_t* ka, uint32_t* va, u
   Control* ctl = at<Control>(ws, L.ctl);
   const uint64_t stride = static_cast<uint64_t>(L.ntiles) * (1u << RB);
   const bool narrow = narrow_words(n);
-  const int shape = sort_arrays_shape(n);
+  const int shape = pass_shape(n, true);  // (uniform keys: 4.2M pairs, one pass, 65 us against 69 in 512 x 16)
   const uint32_t ntiles = static_cast<uint32_t>(ceil_div(n, sort_shape_tile(shape)));
   const bool copied = plan.sp.passes % 2 != 0;
   {
