@@ -457,37 +457,48 @@ struct Build {
 // that choose another pair generation are about the pairs themselves.
 bool records_allowed() { return g_build_path == 0 && !g_fused_expand && !g_per_object_pairs; }
 
-// Builds by records from this many pairs, and below it from this many pairs a
-// triangle: a box of one or two cells is about as many records as pairs, and the
-// records' extra steps then cost more than their passes save.  Measured, us by
-// pairs and by records: 4.3M pairs at 2.2 a triangle 199 and 294, 2.1M at 2.1 161
-// and 180, 4.3M at 4.3 196 and 173, 3.5M at 3.5 201 and 176, 54M at 5.4 1190 and
-// 860, 30M at 30 635 and 302; up to 2^18 pairs the two are within 4%.
-constexpr uint64_t kRecordsFew = uint64_t{1} << 18;
-bool records_pay(uint64_t pairs, uint64_t ntris) { return pairs <= kRecordsFew || 4 * pairs >= 13 * ntris; }
+// Where a build by records is the faster one.  A box of one or two cells is about
+// as many records as pairs, and the records' extra steps then cost more than
+// their passes save; and a scene whose pairs crowd into few segments (arch-like
+// and mesh scenes of few triangles) leaves them to few workgroups.  Us by pairs
+// and by records (pairs, pairs per triangle, passes by either):
+//  - large: 54M at 5.4 1190 / 845, 30M at 30 635 / 300, 4.3M at 4.3 196 / 173, 3.5M
+//    at 3.5 201 / 176; 2.1M at 2.1 161 / 180, 4.3M at 2.2 199 / 294.
+//  - below 2^21: 816k at 4.1 119 / 111, 1.2M at 6 137 / 113, 1.8M at 51 153 / 111;
+//    mesh of 666k at 3.3 121 / 140, 419k at 3.8 114 / 126.
+//  - below 2^19 the steps cost 6 us more, so a pass has to fall away: from three 160k
+//    at 4.6 102 / 97, 161k at 2.7 105 / 96, but arch-like 95k at 1.6 102 / 126; from
+//    two 9k at 2 83 / 75, 6k at 1.3 78 / 68, but arch-like 13k at 1.1 86 / 131.  With
+//    as many passes 278k at 14 91 / 99, 56k at 2.8 88 / 99.
+bool records_pay(uint64_t pairs, uint64_t ntris, int pair_passes, int record_passes) {
+  if (pairs < uint64_t{1} << 19 && record_passes >= pair_passes) return false;
+  if (pairs <= uint64_t{1} << 18) return record_passes == 1 ? 4 * pairs >= 5 * ntris : pairs >= 2 * ntris;
+  return pairs < uint64_t{1} << 21 ? pairs >= 4 * ntris : 4 * pairs >= 13 * ntris;
+}
 
 // A culled build's records are rows of the boxes, each tested once per axis, so
 // what they save grows with the boxes.  Box pairs per triangle -> the build by
 // tested pairs against this one, us: 1.3 (100k arch-like) 129 / 160, 2.1 (1M) 226
 // / 244, 2.5 (100k uniform) 135 / 127, 3.0 (3M arch-like) 584 / 543, 5.4 (10M)
-// 2169 / 1776, 30 (1M mixed) 586 / 359, 446 (1M hairball-like) 3590 / 1600.  Small
-// builds are launches: below 2^20 box pairs this path's own 6 us (8k to 30k
-// hairball-like: 104 / 111, 115 / 126) pay only where a radix pass falls away (2k:
-// 98 / 88); at 1.4M box pairs (300k mixed) 165 / 147.
-constexpr uint64_t kCullRecordsFew = uint64_t{1} << 20;
+// 2169 / 1776, 30 (1M mixed) 586 / 359, 446 (1M hairball-like) 3590 / 1600.  The
+// path's own 6 us (8k to 64k hairball-like: 104 / 111, 115 / 126, 131 / 137) pay in
+// small builds only where a radix pass falls away (2k: 98 / 88; 300k mixed 165 /
+// 147); at 6.6M box pairs (100k) 216 / 187.
+constexpr uint64_t kCullRecordsFew = uint64_t{1} << 22;
 bool cull_records_pay(uint64_t box_pairs, uint64_t ntris, int pair_passes, int record_passes) {
   return 5 * box_pairs >= 12 * ntris && (box_pairs >= kCullRecordsFew || record_passes < pair_passes);
 }
 
 // Makes b a build by records when its grids, about `pairs` pairs, allow it and the workspace holds it.
 void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t cap, uint64_t pairs, size_t ws_bytes) {
-  if (b.ntris == 0 || cap == 0 || (!b.culled && !records_pay(pairs, b.ntris))) return;
+  if (b.ntris == 0 || cap == 0) return;
   RecordPlan rp{};
   Layout L{};
   // a workspace too small for the list of segments: wider segments, fewer of them
   for (uint32_t wider = 0;; ++wider) {
     if (!plan_records(grids, ngrids, cells, pairs, wider, b.culled, &rp)) return;
-    if (b.culled && !cull_records_pay(cap, b.ntris, b.plan.sp.passes, rp.plan.sp.passes)) return;
+    const int pp = b.plan.sp.passes, rpp = rp.plan.sp.passes;
+    if (!(b.culled ? cull_records_pay(cap, b.ntris, pp, rpp) : records_pay(pairs, b.ntris, pp, rpp))) return;
     L = make_record_layout(b.ntris, cap, rp, ngrids, b.batched, b.culled);
     if (L.total <= ws_bytes) break;
   }
@@ -1030,7 +1041,9 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
   const SortPlan& sp = b.plan.sp;
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
-  b.sort_shape = build_sort_shape((b.culled ? std::min(npairs, b.out_cap) : npairs) / 2, true);
+  // records of about so many: rows of boxes as wide as high, and no more than half the pairs
+  const double np = static_cast<double>(b.culled ? std::min(npairs, b.out_cap) : npairs), rows = std::cbrt(np / b.ntris);
+  b.sort_shape = build_sort_shape(static_cast<uint64_t>(std::min(np / 2, rows * rows * b.ntris)), true);
   b.rec_cap = npairs;
   const Dest bufs[2] = {{at<uint32_t>(b.ws, b.L.keys_alt), at<uint32_t>(b.ws, b.L.vals_alt)},
                         B ? Dest{at<uint32_t>(b.ws, b.L.keys_alt2), at<uint32_t>(b.ws, b.L.vals_alt2)}

@@ -68,8 +68,10 @@ def _build(G, s, by_records=True):
     (256, 7, 9), (257, 2, 30), (1024, 3, 3), (1, 1024, 1), (1, 1, 1024), (3, 1024, 2), (1000, 1, 2)])
 def test_segment_shapes(G, res):
     rng = np.random.default_rng(res[0] * 7 + res[1])
-    lo, hi = _random(rng, 4099, res, (40, 4, 3))
-    _build(G, _boxes(lo, hi, res, f"shapes{res}"))
+    lo, hi = _random(rng, 140_001, res, (40, 40, 40))
+    total = np.cumsum(np.prod(hi - lo + 1, 1))
+    n = min(int(np.searchsorted(total, 1 << 19)) + 1, len(total))  # as many pairs as a build by records takes
+    _build(G, _boxes(lo[:n], hi[:n], res, f"shapes{res}"), by_records=total[n - 1] >= 4 * n)
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 256, 257, 999, 1000, 1001, 1999, 2000, 2001, 4095, 4096, 4097, 12289])
@@ -109,7 +111,7 @@ def test_empty_stretches(G, at):
 def test_outputs_aligned_to_one_word(G):
     rng = np.random.default_rng(11)
     res = (90, 20, 10)
-    s = _boxes(*_random(rng, 3001, res, (9, 3, 2)), res, "unaligned")
+    s = _boxes(*_random(rng, 60_001, res, (9, 3, 2)), res, "unaligned")
     g = G.GridInput.from_scene(s)
     n, _ = G.count(g)
 
@@ -121,13 +123,21 @@ def test_outputs_aligned_to_one_word(G):
 
 def test_batched_grids_share_tiles(G):
     rng = np.random.default_rng(3)
-    shapes = [((40, 30, 20), 900), ((1, 1, 1), 3), ((300, 2, 5), 50), ((8, 8, 8), 0), ((16, 16, 16), 5000), ((200, 100, 9), 20),
-              ((64, 64, 4), 9000), ((2, 2, 2), 2500)]
+    shapes = [((40, 30, 20), 900), ((1, 1, 1), 3), ((300, 2, 5), 50), ((8, 8, 8), 0), ((16, 16, 16), 20_000), ((200, 100, 9), 20),
+              ((64, 64, 4), 36_000), ((2, 2, 2), 2500)]
     ss = [_boxes(*_random(rng, n, res, (12, 4, 3)), res, f"b{i}") if n else
           scenes.Scene("empty", np.zeros((3, 0), np.float32), np.zeros((0, 3), np.uint32), np.zeros(3, np.float32),
                        np.ones(3, np.float32), np.asarray(res, np.uint32)) for i, (res, n) in enumerate(shapes)]
     inputs = [G.GridInput.from_scene(s) for s in ss]
-    for r, s in zip(G.build_batched(inputs), ss):
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        results = G.build_batched(inputs)
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+    assert "finish" in k, sorted(k)
+    for r, s in zip(results, ss):
         torch.cuda.synchronize()
         if s.ntris:
             _same(r, s)
@@ -136,10 +146,11 @@ def test_batched_grids_share_tiles(G):
 
 
 def test_few_pairs_a_triangle_sort_pairs(G):
-    # 300,000 pairs of one or two cells: by pairs; the same number in larger boxes: by records
+    # pairs of one cell each: by pairs; more of them in larger boxes: by records; few, unless a pass falls away: by pairs
     rng = np.random.default_rng(8)
     res = (120, 60, 30)
     lo, _ = _random(rng, 300_000, res, (1, 1, 1))
     _build(G, _boxes(lo, lo, res, "points"), by_records=False)
-    lo, hi = _random(rng, 60_000, res, (5, 3, 2))
+    lo, hi = _random(rng, 160_000, res, (5, 3, 2))
     _build(G, _boxes(lo, hi, res, "boxes"), by_records=True)
+    _build(G, _boxes(lo[:40_000], hi[:40_000], res, "fewer boxes"), by_records=False)
