@@ -621,9 +621,12 @@ int pass_shape(uint64_t n, bool estimate) {
   return !estimate && tiles > cus && 2 * tiles <= 3 * cus ? 0 : 3;
 }
 
-// The sort_shape knob's, where pass_shape would take its default.
-int build_sort_shape(uint64_t n, bool estimate) {
+// The sort_shape knob's, where pass_shape would take its default.  Batches of at
+// most eight such tiles of pairs, whose last pass looks each pair's grid up, keep
+// 256 x 16 (one grid of 62K pairs: 118 and 121 us).
+int build_sort_shape(uint64_t n, bool estimate, bool batched = false) {
   const int shape = g_small_tiles ? pass_shape(n, estimate) : 3;
+  if (shape == 2 && batched && !estimate && n <= 8 * 16384) return 1;
   return shape == 3 ? g_sort_shape : shape;
 }
 
@@ -919,7 +922,7 @@ int launch_sort_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t n
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
   const bool fused = fused_first_pass(b);
-  b.sort_shape = build_sort_shape(npairs, false);  // before anything sizes or clears the passes' look-back words
+  b.sort_shape = build_sort_shape(npairs, false, B);  // before anything sizes or clears the passes' look-back words
   const uint32_t* in_k = nullptr;
   const uint32_t* in_v = nullptr;
   if (fused) {
@@ -1410,7 +1413,9 @@ int grid_build_culled(const float* verts_soa, uint32_t nverts, const uint32_t* t
   b.culled = true;
   b.out_cap = out->cap_pairs;
   if (records_allowed() && out->cap_pairs > 0)
-    try_records(b, &b.gs.one, 1, ncells_of(res), box_cap, std::min(box_cap, out->cap_pairs), ws_bytes);
+    // (outputs may be sized for the box pairs: segments as for eight kept pairs a cell at most, since a
+    // narrower segment is more records for the same rows: 1M hairball-like 3940 us at four cells)
+    try_records(b, &b.gs.one, 1, ncells_of(res), box_cap, std::min({box_cap, out->cap_pairs, 8 * ncells_of(res)}), ws_bytes);
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
   b.gs.one.out_ranges = out->ranges;
