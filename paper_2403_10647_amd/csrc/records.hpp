@@ -228,107 +228,107 @@ __global__ __launch_bounds__(Block) void seg_list_kernel(SegListArgs a) {
   const uint32_t ck = a.code.ck, wx = a.code.wx;
   const uint32_t xmask = (1u << wx) - 1u, ymask = (1u << a.code.wy) - 1u;
   while (true) {
-  const uint32_t tile = next_tile(&a.ctl->tile_counter[kCtrSplit], &s_tile);
-  if (tile >= ntiles) return;
-  const uint64_t wbase = static_cast<uint64_t>(tile) * N + static_cast<uint64_t>(w) * (Q * kGroup);
-  // the wave's records that exist; past them a lane repeats the last record of
-  // the list, which is no head and whose pairs are left out
-  const uint32_t n = static_cast<uint32_t>(wbase >= nrec ? 0 : nrec - wbase < Q * kGroup ? nrec - wbase : Q * kGroup);
-  const uint32_t* keys = a.keys + (wbase < nrec ? wbase : 0);
-  uint32_t key[Q][4];
-  if (n == Q * kGroup && a.vec16) {
+    const uint32_t tile = next_tile(&a.ctl->tile_counter[kCtrSplit], &s_tile);
+    if (tile >= ntiles) return;
+    const uint64_t wbase = static_cast<uint64_t>(tile) * N + static_cast<uint64_t>(w) * (Q * kGroup);
+    // the wave's records that exist; past them a lane repeats the last record of
+    // the list, which is no head and whose pairs are left out
+    const uint32_t n = static_cast<uint32_t>(wbase >= nrec ? 0 : nrec - wbase < Q * kGroup ? nrec - wbase : Q * kGroup);
+    const uint32_t* keys = a.keys + (wbase < nrec ? wbase : 0);
+    uint32_t key[Q][4];
+    if (n == Q * kGroup && a.vec16) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint4 v = reinterpret_cast<const uint4*>(keys)[q * kWave + lane];
+        key[q][0] = v.x;
+        key[q][1] = v.y;
+        key[q][2] = v.z;
+        key[q][3] = v.w;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t i = q * kGroup + 4 * lane + k;
+          key[q][k] = n ? keys[i < n ? i : n - 1] : 0u;
+        }
+    }
+    // the record before the wave's first (none: a segment that does not exist)
+    uint32_t before = n && wbase > 0 ? *(keys - 1) >> ck : 0xFFFFFFFFu;
+    uint32_t head[Q], hx[Q], px[Q];  // head bits of the lane's four records; heads and pairs before them in the wave
+    uint32_t heads = 0, pairs = 0;   // of the wave
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const uint4 v = reinterpret_cast<const uint4*>(keys)[q * kWave + lane];
-      key[q][0] = v.x;
-      key[q][1] = v.y;
-      key[q][2] = v.z;
-      key[q][3] = v.w;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
+      const uint32_t s3 = key[q][3] >> ck;
+      uint32_t last = static_cast<uint32_t>(__shfl_up(static_cast<int>(s3), 1, kWave));
+      if (lane == 0) last = before;
+      before = wave_readlane(s3, kWave - 1);
+      uint32_t h = 0, p = 0;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t i = q * kGroup + 4 * lane + k;
-        key[q][k] = n ? keys[i < n ? i : n - 1] : 0u;
+        const uint32_t seg = key[q][k] >> ck;
+        const bool in = q * kGroup + 4 * lane + k < n;
+        h |= (in && seg != last ? 1u : 0u) << k;
+        last = seg;
+        p += in ? __umul24((key[q][k] & xmask) + 1u, ((key[q][k] >> wx) & ymask) + 1u) : 0u;
       }
-  }
-  // the record before the wave's first (none: a segment that does not exist)
-  uint32_t before = n && wbase > 0 ? *(keys - 1) >> ck : 0xFFFFFFFFu;
-  uint32_t head[Q], hx[Q], px[Q];  // head bits of the lane's four records; heads and pairs before them in the wave
-  uint32_t heads = 0, pairs = 0;   // of the wave
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const uint32_t s3 = key[q][3] >> ck;
-    uint32_t last = static_cast<uint32_t>(__shfl_up(static_cast<int>(s3), 1, kWave));
-    if (lane == 0) last = before;
-    before = wave_readlane(s3, kWave - 1);
-    uint32_t h = 0, p = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t seg = key[q][k] >> ck;
-      const bool in = q * kGroup + 4 * lane + k < n;
-      h |= (in && seg != last ? 1u : 0u) << k;
-      last = seg;
-      p += in ? __umul24((key[q][k] & xmask) + 1u, ((key[q][k] >> wx) & ymask) + 1u) : 0u;
+      const uint32_t hc = static_cast<uint32_t>(__builtin_popcount(h));
+      const uint32_t hi = wave_inclusive(hc, OpAdd{}), pi = wave_inclusive(p, OpAdd{});
+      head[q] = h;
+      hx[q] = heads + hi - hc;
+      px[q] = pairs + pi - p;
+      heads += wave_readlane(hi, kWave - 1);
+      pairs += wave_readlane(pi, kWave - 1);
     }
-    const uint32_t hc = static_cast<uint32_t>(__builtin_popcount(h));
-    const uint32_t hi = wave_inclusive(hc, OpAdd{}), pi = wave_inclusive(p, OpAdd{});
-    head[q] = h;
-    hx[q] = heads + hi - hc;
-    px[q] = pairs + pi - p;
-    heads += wave_readlane(hi, kWave - 1);
-    pairs += wave_readlane(pi, kWave - 1);
-  }
-  if (lane == 0) {
-    s_heads[w] = heads;
-    s_pairs[w] = pairs;
-  }
-  __syncthreads();
-  uint32_t hw = 0, pw = 0, ht = 0, pt = 0;  // before this wave in the tile; the tile's totals
-#pragma unroll
-  for (int i = 0; i < W; ++i) {
-    const uint32_t h = s_heads[i], p = s_pairs[i];
-    hw += static_cast<uint32_t>(i) < w ? h : 0u;
-    pw += static_cast<uint32_t>(i) < w ? p : 0u;
-    ht += h;
-    pt += p;
-  }
-  if (w == 0) {
-    const uint64_t total = (static_cast<uint64_t>(ht) << 33) + pt;
-    const uint64_t p = lookback_wave(a.status, tile, total);
     if (lane == 0) {
-      s_prefix = p;
-      if (tile == ntiles - 1) {
-        const uint64_t all = p + total;
-        const uint32_t nheads = static_cast<uint32_t>(all >> 33);
-        const uint64_t npairs = all & ((uint64_t{1} << 33) - 1);
-        // the records must hold exactly the pairs the count added up
-        if (npairs != a.ctl->npairs || nheads > a.list_cap) {
-          atomicOr(&a.ctl->error, kErrInternal);
-        } else {
-          a.list[nheads] = {a.code.nsegs, static_cast<uint32_t>(nrec), static_cast<uint32_t>(npairs), 0u};
-          a.ctl->nlist = nheads;
+      s_heads[w] = heads;
+      s_pairs[w] = pairs;
+    }
+    __syncthreads();
+    uint32_t hw = 0, pw = 0, ht = 0, pt = 0;  // before this wave in the tile; the tile's totals
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      const uint32_t h = s_heads[i], p = s_pairs[i];
+      hw += static_cast<uint32_t>(i) < w ? h : 0u;
+      pw += static_cast<uint32_t>(i) < w ? p : 0u;
+      ht += h;
+      pt += p;
+    }
+    if (w == 0) {
+      const uint64_t total = (static_cast<uint64_t>(ht) << 33) + pt;
+      const uint64_t p = lookback_wave(a.status, tile, total);
+      if (lane == 0) {
+        s_prefix = p;
+        if (tile == ntiles - 1) {
+          const uint64_t all = p + total;
+          const uint32_t nheads = static_cast<uint32_t>(all >> 33);
+          const uint64_t npairs = all & ((uint64_t{1} << 33) - 1);
+          // the records must hold exactly the pairs the count added up
+          if (npairs != a.ctl->npairs || nheads > a.list_cap) {
+            atomicOr(&a.ctl->error, kErrInternal);
+          } else {
+            a.list[nheads] = {a.code.nsegs, static_cast<uint32_t>(nrec), static_cast<uint32_t>(npairs), 0u};
+            a.ctl->nlist = nheads;
+          }
         }
       }
     }
-  }
-  __syncthreads();
-  const uint32_t j0 = static_cast<uint32_t>(s_prefix >> 33) + hw, p0 = static_cast<uint32_t>(s_prefix) + pw;  // (pairs < 2^32)
+    __syncthreads();
+    const uint32_t j0 = static_cast<uint32_t>(s_prefix >> 33) + hw, p0 = static_cast<uint32_t>(s_prefix) + pw;  // (pairs < 2^32)
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    uint32_t j = j0 + hx[q], pos = p0 + px[q];
+    for (int q = 0; q < Q; ++q) {
+      uint32_t j = j0 + hx[q], pos = p0 + px[q];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if ((head[q] >> k) & 1u) {
-        if (j < a.list_cap)
-          a.list[j] = {key[q][k] >> ck, static_cast<uint32_t>(wbase) + q * kGroup + 4 * lane + k, pos, 0u};
-        ++j;
+      for (int k = 0; k < 4; ++k) {
+        if ((head[q] >> k) & 1u) {
+          if (j < a.list_cap)
+            a.list[j] = {key[q][k] >> ck, static_cast<uint32_t>(wbase) + q * kGroup + 4 * lane + k, pos, 0u};
+          ++j;
+        }
+        pos += __umul24((key[q][k] & xmask) + 1u, ((key[q][k] >> wx) & ymask) + 1u);
       }
-      pos += __umul24((key[q][k] & xmask) + 1u, ((key[q][k] >> wx) & ymask) + 1u);
     }
-  }
   }
 }
 
