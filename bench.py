@@ -32,10 +32,14 @@ HBM_PEAK_GBS = 8000.0     # MI355X HBM3E
 PROFILES = os.path.join(ROOT, "profiles")
 
 
-def kernel_bytes(name: str, T: int, NO: int, R: int) -> float:
+def kernel_bytes(name: str, T: int, NO: int, R: int, records: bool = False) -> float:
     """Algorithmic bytes one launch of `name` must move: each input read once and
     each output written once, for T triangles, NO pairs and R cells (look-back
-    words, histograms and re-reads are not counted)."""
+    words, histograms and re-reads are not counted).  A build by records
+    (`records`) keeps their number to itself: what its kernels move of them is
+    not counted either, so its radix passes have no figure here."""
+    if records and name.startswith("onesweep"):
+        return 0.0
     return {
         "count_scan": 60.0 * T,            # 12 B indices + 36 B vertices in, 4 B start + 8 B box out
         "expand_hist": 12.0 * T + 8.0 * NO,  # start + box in, object-order pairs out
@@ -44,7 +48,22 @@ def kernel_bytes(name: str, T: int, NO: int, R: int) -> float:
         "onesweep": 16.0 * NO,             # pairs in, pairs out
         "expand": 12.0 * T + 8.0 * NO,
         "ranges": 4.0 * NO + 8.0 * R,      # sorted cells in, (begin, end) per cell out
+        "records": 12.0 * T,               # start + box in
+        "finish": 8.0 * NO + 8.0 * R,      # pairs and (begin, end) per cell out
     }.get(name, 0.0)
+
+
+def dominant(kernels: dict, T: int, NO: int, R: int):
+    """The kernel that takes the most time, of those whose bytes are known, with its bytes per
+    launch, its launches and its total ms.  The kernels that finish a build by records share its
+    segments out by size and count as one."""
+    records = "finish" in kernels
+    k = dict(kernels)
+    if records:
+        k["finish"] = (k["finish"][0], sum(v[1] for n, v in kernels.items() if n.startswith("finish")))
+    known = {n: kernel_bytes(n, T, NO, R, records) for n in k}
+    name = max((n for n in k if known[n] > 0.0) if any(known.values()) else k, key=lambda n: k[n][1])
+    return name, known[name], k[name][0], k[name][1]
 
 
 def survey_bytes(T: int, NO: int, R: int, passes: int) -> int:
@@ -181,9 +200,8 @@ def run_configs(G, args, steps: int = 20) -> dict:
         k = G.trace_read()
         G.trace_enable(False)
         T, R = s.ntris, s.ncells
-        dom = max(k, key=lambda x: k[x][1])
-        avg = k[dom][1] / k[dom][0]
-        bpl = kernel_bytes(dom, T, n, R)
+        dom, bpl, launches, total = dominant(k, T, n, R)
+        avg = total / launches
         passes = G.sort_plan(max(0, (R - 1).bit_length()))[0]
         bs = survey_bytes(T, n, R, passes)
         res[name] = {"triangles": T, "npairs": n, "cells": R, "ms_per_build": round(ms, 4),
@@ -269,14 +287,19 @@ def run_batched(G, args) -> dict:
     cells_tot = sum(g.ncells for g in inputs)
     plan = G.sort_plan(max(1, (cells_tot - 1).bit_length()))
     b_survey = sum(survey_bytes(s.ntris, c, s.ncells, plan[0]) for s, c in zip(batch, caps))
-    sweeps = [(k, v) for k, v in kern.items() if k.startswith("onesweep")]
+    # by records the passes move records, whose number stays on the device: the finish instead
+    group, bpl = ("finish", 8 * int(ntot) + 8 * int(cells_tot)) if "finish" in kern else ("onesweep", 16 * int(ntot))
+    sweeps = [(k, v) for k, v in kern.items() if k.startswith(group)]
     sw_launch, sw_ms = sum(v[0] for _, v in sweeps), sum(v[1] for _, v in sweeps)
+    if group == "finish":
+        sw_launch = kern["finish"][0]  # its kernels share one build's segments
     batch_roof = None
     if sw_launch:
         avg = sw_ms / sw_launch
-        batch_roof = {"kernel": "onesweep (all passes)", "avg_launch_ms": round(avg, 5),
-                      "bytes_per_launch": 16 * int(ntot), "achieved": round(16 * ntot / (avg * 1e-3) / 1e9, 1),
-                      "peak": HBM_PEAK_GBS, "frac": round(16 * ntot / (avg * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
+        batch_roof = {"kernel": "onesweep (all passes)" if group == "onesweep" else "finish (all its kernels)",
+                      "avg_launch_ms": round(avg, 5), "bytes_per_launch": bpl,
+                      "achieved": round(bpl / (avg * 1e-3) / 1e9, 1),
+                      "peak": HBM_PEAK_GBS, "frac": round(bpl / (avg * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     res = {"ngrids": len(inputs), "triangles": int(sum(s.ntris for s in batch)), "npairs": int(ntot),
            "cells": int(cells_tot), "bytes_survey_model": int(b_survey),
            "frac_survey_model": round(b_survey / tb / 1e9 / HBM_PEAK_GBS, 4), "roofline": batch_roof,
@@ -327,8 +350,10 @@ def run_ablation(G, args, gin, out, ws, reps: int = 5) -> dict:
                 G.tune_set("per_object_pairs", 0)
             same = (torch.equal(o.cells[:n], ref.cells[:n]) and torch.equal(o.objs[:n], ref.objs[:n])
                     and torch.equal(o.ranges, ref.ranges))
+            # by records the pairs are made at the end, from the records: both steps count
+            names = [gen] if gen in k else [x for x in k if x == "records" or x.startswith("finish")]
             row[label] = {"ms_per_build": round(wall, 4),
-                          "pair_generation_ms": round(k[gen][1] / k[gen][0], 4) if gen in k else None,
+                          "pair_generation_ms": round(sum(k[x][1] / k[x][0] for x in names), 4) if names else None,
                           "identical_to_default": bool(same)}
             del o, run
         a, b = row["per_pair"]["pair_generation_ms"], row["per_object"]["pair_generation_ms"]
@@ -636,14 +661,14 @@ def main():
     torch.cuda.synchronize()
     kern_all = G.trace_read()
     G.trace_enable(False)
-    dom = max(kern_all, key=lambda k: kern_all[k][1]) if kern_all else None
+    dom, bpl, launches, tot_ms = dominant(kern_all, T, NO, R) if kern_all else (None, 0.0, 0, 0.0)
 
     # the timed region: K builds; events bracket only the dominant kernel's
     # launches (on the stream they are launched on), for its roofline.  When
     # that kernel is the radix pass, one pair of events spans a build's passes
     # (which run back to back), so that the timed builds carry two event
     # records each instead of two per pass
-    trace = not args.no_trace and dom is not None
+    trace = not args.no_trace and dom is not None and dom != "finish"  # (several kernels: the traced run's times)
     span = dom == "onesweep" and all(k == "onesweep" or not k.startswith("onesweep") for k in kern_all)
     if trace:
         G.trace_only("radix_passes" if span else dom)
@@ -670,10 +695,9 @@ def main():
         if span and "radix_passes" in kern:
             # the span's total over the passes it covers
             launches, tot_ms = kern_all[dom][0], kern["radix_passes"][1]
-        else:
-            launches, tot_ms = kern[dom] if dom in kern else kern_all[dom]
+        elif dom in kern:
+            launches, tot_ms = kern[dom]
         avg_ms = tot_ms / launches
-        bpl = kernel_bytes(dom, T, NO, R)
         achieved = bpl / (avg_ms * 1e-3) / 1e9
         traffic = load_traffic(dom, args.workload, knobs)
         roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -681,7 +705,7 @@ def main():
                     "avg_launch_ms": round(avg_ms, 5), "bytes_per_launch": int(bpl),
                     "events": ("timed region, one span over each build's passes" if span and "radix_passes" in kern
                                else "timed region" if dom in kern else "separate traced run")}
-        b_alg = sum(kernel_bytes(k, T, NO, R) * v[0] for k, v in kern_all.items()) / args.steps
+        b_alg = sum(kernel_bytes(k, T, NO, R, "finish" in kern_all) * v[0] for k, v in kern_all.items()) / args.steps
         kern_ms = sum(v[1] for v in kern_all.values()) / args.steps
         passes = G.sort_plan(max(0, (R - 1).bit_length()))[0]
         b_survey = survey_bytes(T, NO, R, passes)
