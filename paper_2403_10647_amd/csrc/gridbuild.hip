@@ -1064,7 +1064,6 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
     a.o.vec16 = ((reinterpret_cast<uintptr_t>(d.k) | reinterpret_cast<uintptr_t>(d.v)) & 15u) == 0;
     a.o.ctl = ctl;
     a.code = b.code;
-    a.run = at<GridRun>(b.ws, b.L.run);
     if (!B && b.culled) {
       int st = launch_cull_rows<RB>(b, a, P % 2 ? b.out_cap : npairs, npairs);
       if (st) return st;
@@ -2085,7 +2084,13 @@ int grid_build_batched_counted(const grid_desc* grids, uint32_t ngrids, void* ws
   // a grid beyond its capacity is caught by the sink kernel, pairs beyond the
   // workspace by the count's plan, and either way no kernel writes anything
   const uint64_t n = std::min<uint64_t>(bs.cap, b.layout_cap);
-  if (b.rec) return launch_records<true>(b, nullptr, nullptr, std::max<uint64_t>(n, 1));
+  if (b.rec) {
+    // the plan again, now with the outputs' capacities: a grid beyond its own is
+    // flagged by a kernel that ends before the first one that acts on the flag
+    // begins (workgroups of one kernel that raise it and read it race)
+    if ((st = launch_plan<true>(b))) return st;
+    return launch_records<true>(b, nullptr, nullptr, std::max<uint64_t>(n, 1));
+  }
   if (n > 0) {
     if (b.plan.sp.passes == 0) return GRID_E_INVAL;
     if ((st = launch_sort<true>(b, nullptr, nullptr, n))) return st;

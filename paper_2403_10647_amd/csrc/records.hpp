@@ -40,7 +40,6 @@ struct SegCode {
 struct RecordArgs {
   ExpandOutArgs o;          // cells/objs receive the records' keys and values
   SegCode code;
-  const GridRun* run;       // batched: each grid's pair count
 };
 
 // What the expansion needs of an object's grid.
@@ -147,12 +146,6 @@ __global__ __launch_bounds__(Block, 8) void record_kernel(RecordArgs a) {
   if (build_failed(a.o.ctl)) return;
   const uint64_t nrec = a.o.ctl->nitems;
   const uint32_t ntiles = static_cast<uint32_t>((nrec + N - 1) / N);
-  if constexpr (Batched) {
-    // outputs may have been given after the count (a build resumed from its
-    // count): their capacities are checked again before the kernel that writes them
-    for (uint32_t g = blockIdx.x * Block + threadIdx.x; g < a.o.ex.gs.ngrids; g += gridDim.x * Block)
-      if (a.run[g].npairs > a.o.ex.gs.table[g].cap_pairs) atomicOr(&a.o.ctl->cap_flag, 1u);
-  }
   clear_status<Block>(a.o.clear, nrec);
   for (uint32_t i = threadIdx.x; i < a.o.plan.passes * R; i += Block) s_hist[i] = 0;
   __syncthreads();

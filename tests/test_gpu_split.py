@@ -205,3 +205,34 @@ def test_split_builds_interleaved_on_two_streams(G):
     assert G.workspace_status(wa, sa)[0] == G.GRID_OK and G.workspace_status(wb, sb)[0] == G.GRID_OK
     _oracle_equal(oa, a)
     _oracle_equal(ob, b)
+
+
+def test_split_by_records_checks_capacities_before_its_kernels(G):
+    # a batch that is built by records: the outputs' capacities are checked by a kernel of their own (the plan,
+    # run again once the outputs are known), so no workgroup can meet the flag half raised
+    batch = _batch(48, [60_000, 50_000, 70_000])
+    inputs = [G.GridInput.from_scene(s) for s in batch]
+    caps = G.count_batched(inputs)
+    ws = G.Workspace()
+    wsb = _ws_bytes(G, inputs, caps)
+    ws.get(wsb)
+    h = _Half(G, 3)
+    for less in (1, 0):
+        _, counts, status = _count(G, inputs, ws, wsb, h)
+        assert counts == caps and status == 0
+        given = [caps[0], caps[1], caps[2] - less]
+        outs = _filled(G, inputs, given)
+        _say("split by records", given)
+        G.trace_enable(True)
+        G.trace_read()
+        try:
+            G.build_batched_counted(inputs, outs, given, ws, wsb, h.stage)
+        finally:
+            k = G.trace_read()
+            G.trace_enable(False)
+        assert "records" in k and "plan" in k, sorted(k)
+        assert G.workspace_status(ws)[0] == (G.GRID_E_CAPACITY if less else G.GRID_OK)
+        if less:
+            assert _untouched(outs)
+        else:
+            _oracle_equal(outs, batch)
