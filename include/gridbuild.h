@@ -339,8 +339,8 @@ typedef struct grid_trace_entry {
   char name[48];       /* kernel: zero, count_scan, plan, sink, expand, expand_hist, expand_straddle,
                           hist, makepairs, makepairs_hist, onesweep_expand, onesweep,
                           onesweep_grids, split, ranges; builds by records: records,
-                          records_straddle, onesweep, seg_list, finish, finish_mid,
-                          finish_big */
+                          records_straddle, onesweep, seg_list, finish, finish_count,
+                          finish_tasks */
   uint32_t launches;   /* launches since the last read */
   double total_ms;     /* summed event-measured duration */
 } grid_trace_entry;

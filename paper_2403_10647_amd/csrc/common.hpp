@@ -31,7 +31,7 @@ struct Control {
   uint32_t big_n;              // compact builds: cells listed for the workgroup sort
   uint64_t nitems;             // record builds: records of the build (npairs is then the pairs they hold)
   uint32_t nlist;              // record builds: segments that hold a record
-  uint32_t ngaps;              // record builds: very long stretches of empty segments
+  uint32_t crowd;              // record builds: pairs above which a segment is not its wave's alone
 };
 constexpr uint32_t kErrBadIndex = 1u;
 constexpr uint32_t kErrInternal = 2u;  // an internal consistency check failed (the build's output is invalid)

@@ -36,15 +36,11 @@ constexpr int kMergeTile = kRangesBlock * kRangesK;
 constexpr int kRecordBlock = 1024, kRecordK = 4;        // records: the expansion's tiles in more, shorter runs
 constexpr int kSegListBlock = 1024, kSegListK = 16;     // 16384 records per tile of the segment list
 constexpr int kSegListTile = kSegListBlock * kSegListK;
-constexpr int kFinishMidBlock = 256;
-constexpr uint32_t kFinishMidCap = 4096;                // pairs a small workgroup stages
 // Pairs a wave stages, by the cells of its per-cell tables: segments of up to 64
 // cells are the dense grids' (their pairs per segment spread wider, and their
 // tables leave room for it).
 constexpr uint32_t kFinishCap = 1000, kFinishCapDense = 2000;
-constexpr uint64_t kFinishOnePairs = uint64_t{1} << 18;  // builds of at most this many pairs finish in one launch less
-constexpr int kFinishBigBlock = 1024;
-constexpr uint32_t kFinishBigCap = 12288;               // pairs a workgroup stages
+constexpr uint32_t finish_cap(uint32_t bits) { return bits <= 6 ? kFinishCapDense : kFinishCap; }
 constexpr int kScanBlock = 256, kScanK = 8;
 constexpr int kMakePairsBlock = 256;                    // per-object pair generation: one thread per object
 constexpr int kPlanBlock = 1024;
@@ -206,11 +202,11 @@ Plan make_plan(uint32_t bits, int max_digit = -1) {
 
 struct Layout {
   size_t ctl, hist, count_status, cull_status, cell_status, zero_end;
-  size_t grid_pairs, list_status, list, gaps;  // record builds
+  size_t grid_pairs, list_status, ntasks, list, tasks, rows, groups;  // record builds
   size_t start, box, tfo, tfg, tfo_work, cull_rec, sort_status, keys_alt, vals_alt, keys_alt2, vals_alt2, run, npairs_out, splits,
       tile_grid, table, sink, kmap, ksink, total;
   uint32_t ntfo, ncount_tiles, nsort_tiles_cap, nmerge_tiles_cap;
-  uint32_t list_cap, gap_cap;
+  uint32_t list_cap, task_lists, task_cap;
 };
 
 Layout make_layout(uint64_t ntris, uint64_t cap_pairs, uint64_t ncells_plus_grids, const Plan& plan,
@@ -348,12 +344,19 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.nsort_tiles_cap = static_cast<uint32_t>(ceil_div(cap_pairs, kSortTileMin));
   L.ntfo = L.nsort_tiles_cap + 1;
   L.list_cap = static_cast<uint32_t>(std::min<uint64_t>(rp.code.nsegs, cap_pairs));
-  L.gap_cap = rp.code.nsegs / (kGapBlock >> (rp.code.wx + rp.code.wy)) + 2;
+  // lists of tasks: a wave adds at most four entries (and the first one more), and
+  // there are no more crowded segments and long stretches than pairs and segments allow
+  const uint32_t bits = rp.code.wx + rp.code.wy, blocks = static_cast<uint32_t>(ceil_div(L.list_cap, kFinishRun));
+  L.task_lists = 1;
+  while (L.task_lists < kTaskLists && L.task_lists * 128 < blocks) L.task_lists *= 2;
+  L.task_cap = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(blocks, L.task_lists) * 4 + 1,
+                                                        cap_pairs / kCrowdLeast + rp.code.nsegs / (kGapWave >> bits) + 2));
   L.ctl = take(sizeof(Control));
   L.hist = take(static_cast<size_t>(kHistCopies) * 4 * kRadixMax * sizeof(uint32_t));
   L.count_status = take(std::max<size_t>(L.ncount_tiles, 1) * 8);
   L.grid_pairs = take(static_cast<size_t>(ngrids) * 8);
   L.list_status = take((ceil_div(cap_pairs, kSegListTile) + 1) * 8);
+  L.ntasks = take(static_cast<size_t>(L.task_lists) * kTaskStride * 8);
   L.cull_status = take(culled ? static_cast<size_t>(L.ntfo) * 8 : 0);
   L.zero_end = o;
   L.start = take(ntris * 4);
@@ -362,8 +365,17 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.tfg = take(batched ? static_cast<size_t>(L.ntfo) * 4 : 0);
   L.tfo_work = take(tfo_work_cap(L.ntfo) * sizeof(uint4));
   L.cull_rec = take(culled ? ntris * sizeof(CullRecord) : 0);
-  L.sort_status = take(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
-                       (narrow_words(cap_pairs) ? 4 : 8));
+  // the tasks and the chunks' counts come after the radix passes, where those keep their
+  // look-back words (rows only where a segment can hold several chunks)
+  const uint64_t chunks = cap_pairs < 2 * kChunkPairs ? 0 : ceil_div(cap_pairs, kChunkPairs);
+  const uint64_t groups = chunks < 2 * kGroupChunks ? 0 : ceil_div(chunks, kGroupChunks);
+  const size_t tasks_size = align_up(static_cast<size_t>(L.task_lists) * L.task_cap * sizeof(uint2));
+  L.sort_status = take(std::max(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
+                                    (narrow_words(cap_pairs) ? 4 : 8),
+                                tasks_size + ((chunks + groups) << bits) * 4));
+  L.tasks = L.sort_status;
+  L.rows = L.tasks + tasks_size;
+  L.groups = L.rows + (chunks << bits) * 4;
   L.keys_alt = take(cap_pairs * 4);
   L.vals_alt = take(cap_pairs * 4);
   L.keys_alt2 = take(batched ? cap_pairs * 4 : 0);
@@ -372,7 +384,6 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.npairs_out = take((ngrids + 1) * 8);
   L.table = take(batched ? ngrids * sizeof(GridDev) : 0);
   L.list = take((static_cast<size_t>(L.list_cap) + 1) * sizeof(SegEntry));
-  L.gaps = take(static_cast<size_t>(L.gap_cap) * 3 * 4);
   L.total = o + 256;
   return L;
 }
@@ -1133,40 +1144,35 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
   a.code = b.code;
   a.list = sl;
   a.list_cap = b.L.list_cap;
-  a.gaps = at<uint32_t>(b.ws, b.L.gaps);
-  a.gap_cap = b.L.gap_cap;
+  a.task_lists = b.L.task_lists;
+  a.task_cap = b.L.task_cap;
+  a.tasks = at<uint2>(b.ws, b.L.tasks);
+  a.ntasks = at<uint64_t>(b.ws, b.L.ntasks);
+  a.rows = at<uint32_t>(b.ws, b.L.rows);
+  a.groups = at<uint32_t>(b.ws, b.L.groups);
   a.ctl = ctl;
   // the LDS per-cell tables are sized for the segments' width
   const uint32_t bits = b.code.wx + b.code.wy;
-  const uint32_t wave_cap = bits <= 6 ? kFinishCapDense : kFinishCap;
   {
     TraceScope ts(b.s, "finish");
-    auto kern = bits <= 6 ? (b.code.wy ? finish_kernel<kFinishCapDense, 64, B, true> : finish_kernel<kFinishCapDense, 64, B, false>)
-              : bits <= 7 ? (b.code.wy ? finish_kernel<kFinishCap, 128, B, true> : finish_kernel<kFinishCap, 128, B, false>)
-                          : (b.code.wy ? finish_kernel<kFinishCap, 256, B, true> : finish_kernel<kFinishCap, 256, B, false>);
+    auto kern = bits <= 6 ? (b.code.wy ? finish_kernel<finish_cap(6), 64, B, true> : finish_kernel<finish_cap(6), 64, B, false>)
+              : bits <= 7 ? (b.code.wy ? finish_kernel<finish_cap(7), 128, B, true> : finish_kernel<finish_cap(7), 128, B, false>)
+                          : (b.code.wy ? finish_kernel<finish_cap(8), 256, B, true> : finish_kernel<finish_cap(8), 256, B, false>);
     kern<<<static_cast<uint32_t>(ceil_div(b.L.list_cap, kFinishRun)), kWave, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
-  {
-    // few pairs: one launch for all that is left (a workgroup that meets more than
-    // its staging holds stores pairs where their ranks put them)
-    const bool all = npairs <= kFinishOnePairs;
-    TraceScope ts(b.s, "finish_mid");
-    auto kern = all ? (b.code.wy ? finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, true, B, true>
-                                 : finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, true, B, false>)
-                    : (b.code.wy ? finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, false, B, true>
-                                 : finish_big_kernel<kFinishMidBlock, kFinishMidCap, true, false, B, false>);
-    kern<<<resident_blocks(kern, kFinishMidBlock, b.L.list_cap), kFinishMidBlock, 0, b.s>>>(a, wave_cap, all ? 0xFFFFFFFFu : kFinishMidCap);
-    GB_LAUNCHED();
-    if (all) return GRID_OK;
-  }
-  {
-    TraceScope ts(b.s, "finish_big");
-    auto kern = b.code.wy ? finish_big_kernel<kFinishBigBlock, kFinishBigCap, false, true, B, true>
-                          : finish_big_kernel<kFinishBigBlock, kFinishBigCap, false, true, B, false>;
-    kern<<<static_cast<uint32_t>(device_cus()), kFinishBigBlock, 0, b.s>>>(a, kFinishMidCap, 0xFFFFFFFFu);
+  // tasks there can be at most: chunks of crowded segments, pieces of long stretches
+  const uint64_t most = npairs / kCrowdLeast + npairs / kChunkPairs + b.code.nsegs / (kGapWave >> bits) + 1;
+  if (npairs >= 2 * kChunkPairs) {  // (no segment of fewer pairs has several chunks)
+    TraceScope ts(b.s, "finish_count");
+    auto kern = b.code.wy ? finish_count_kernel<B, true> : finish_count_kernel<B, false>;
+    kern<<<resident_blocks(kern, kTaskBlock, npairs / kChunkPairs), kTaskBlock, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
+  TraceScope ts(b.s, "finish_tasks");
+  auto kern = b.code.wy ? finish_tasks_kernel<B, true> : finish_tasks_kernel<B, false>;
+  kern<<<resident_blocks(kern, kTaskBlock, most), kTaskBlock, 0, b.s>>>(a);
+  GB_LAUNCHED();
   return GRID_OK;
 }
 

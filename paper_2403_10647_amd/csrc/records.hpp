@@ -13,7 +13,8 @@
 // order, are expanded into its pairs by one wave, which counts them per cell
 // in LDS, writes the cells' ranges from those counts and places every pair at
 // its rank.  Cells and objects are then written once, in order, and the pairs
-// are never read again.
+// are never read again.  Segments of many pairs are cut into chunks of records,
+// which workgroups take in turn, so that the work stays even where a scene crowds.
 //
 // A record's 16 bits of rectangle (first cell, extents) share the sort's 64
 // bits with its segment and its object:
@@ -192,6 +193,18 @@ struct alignas(16) SegEntry {
   uint32_t seg, rec, pair, pad;
 };
 
+// Pairs above which a segment is left to workgroups: the kernel of the waves lasts
+// as long as its longest, so four times the mean of the listed segments and a
+// thousandth of the build's pairs (a wave each on most of the GPU), but no fewer
+// than are worth a workgroup; a wave's staging is the other limit.  Builds, us, at
+// 64 / 256 / 512 / 1000 pairs: 246K pairs in a corner 115 115 115 123; mesh of 4.3M,
+// mean 150, 312 239 226 236; arch-like 54M, mean 260, 1487 1286 999 821.
+constexpr uint32_t kCrowdLeast = 256;
+GB_DEV uint32_t crowded_above(uint64_t npairs, uint32_t nlist) {
+  const uint64_t a = 4 * npairs / nlist, b = npairs / 1024, c = a < b ? a : b;
+  return static_cast<uint32_t>(c > kCrowdLeast ? c : kCrowdLeast);
+}
+
 struct SegListArgs {
   const uint32_t* keys;     // [records] sorted
   SegCode code;
@@ -303,6 +316,7 @@ __global__ __launch_bounds__(Block) void seg_list_kernel(SegListArgs a) {
           } else {
             a.list[nheads] = {a.code.nsegs, static_cast<uint32_t>(nrec), static_cast<uint32_t>(npairs), 0u};
             a.ctl->nlist = nheads;
+            a.ctl->crowd = crowded_above(npairs, nheads);
           }
         }
       }
@@ -328,6 +342,42 @@ __global__ __launch_bounds__(Block) void seg_list_kernel(SegListArgs a) {
 // ---------------------------------------------------------------------------
 // From a segment's records to its pairs and its cells' ranges.
 // ---------------------------------------------------------------------------
+constexpr int kSegCells = 256;          // cells of the widest segment
+
+// What a segment's wave leaves is listed as tasks of about equal size, which the
+// workgroups of the last kernels take in turn however the scene crowds them:
+//  - a segment of more pairs than its wave stages, as chunks of its records (one
+//    workgroup a segment took 3.4 ms for 3.6M pairs in 8 segments; by pairs, whose
+//    work is equal by construction, that whole build is 204 us);
+//  - a stretch of empty segments of more than kGapWave cells, in pieces of about
+//    kGapTask (shorter ones are the wave's of the segment before).
+// kChunkPairs: a chunk's least; a segment below twice as many is one chunk, whose
+// pairs a workgroup stages.  At most kMaxChunks a segment (each reads the counts of
+// those before it), so that chunks grow beyond 4M pairs in one segment.
+constexpr uint32_t kGapWave = 4096, kGapTask = 16384;
+constexpr uint32_t kChunkPairs = 2048, kMaxChunks = 2048;
+constexpr uint32_t kGroupChunks = 32;   // chunks whose counts are also added up together
+constexpr uint32_t kTaskLists = 64;     // most lists (adds to one counter cost 14 ns each, one after another)
+constexpr uint32_t kTaskStride = 16;    // counters of the lists, one a 128-byte line
+constexpr uint32_t kTaskGap = 1u << 31;     // a task entry's stretch of empty segments ...
+constexpr uint32_t kTaskFirst = 0x7FFFFFFFu;  // ... after this list entry (kTaskFirst: before the first one)
+GB_DEV uint32_t gap_segs(const SegCode& c, uint32_t cells) { return cells >> (c.wx + c.wy); }
+GB_DEV uint32_t chunks_of(uint32_t pairs) {
+  const uint32_t c = pairs / kChunkPairs;
+  return c < 2 ? 1u : c < kMaxChunks ? c : kMaxChunks;
+}
+// Chunks take rows of per-cell counts by their segment's pairs: those of [p, p + n)
+// are rows ceil(p / kChunkPairs) on, at most n / kChunkPairs of them, so no two
+// segments share one.  The same holds for groups of kGroupChunks chunks, whose
+// last one is the longer (a segment of fewer than two groups has none).
+GB_DEV uint32_t row_of(uint32_t pair) { return pair / kChunkPairs + (pair % kChunkPairs ? 1u : 0u); }
+GB_DEV uint32_t group_row_of(uint32_t pair) {
+  constexpr uint32_t n = kChunkPairs * kGroupChunks;
+  return pair / n + (pair % n ? 1u : 0u);
+}
+GB_DEV uint32_t row_cells(const SegCode& c) { return 1u << (c.wx + c.wy); }
+GB_DEV uint32_t groups_of(uint32_t chunks) { return chunks < 2 * kGroupChunks ? 0u : chunks / kGroupChunks; }
+
 struct FinishArgs {
   GridSet gs;
   const GridRun* run;
@@ -336,18 +386,14 @@ struct FinishArgs {
   SegCode code;
   const SegEntry* list;     // [list_cap + 1]
   uint32_t list_cap;
-  uint32_t* gaps;           // [3 * gap_cap] (first segment, end segment, pair): the longest stretches of empty segments
-  uint32_t gap_cap;
+  uint32_t task_lists;      // lists of tasks (a power of two) ...
+  uint32_t task_cap;        // ... of so many entries each
+  uint2* tasks;             // [task_lists][task_cap] (list entry | kTaskGap, its first task in this list)
+  uint64_t* ntasks;         // [task_lists * kTaskStride] (zeroed) entries << 32 | tasks
+  uint32_t* rows;           // [ceil(pairs / kChunkPairs)][row_cells] a chunk's pairs per cell
+  uint32_t* groups;         // [ceil(pairs / (kChunkPairs * kGroupChunks))][row_cells] the same of whole groups
   Control* ctl;
 };
-constexpr int kSegCells = 256;          // cells of the widest segment
-
-// Who writes the ranges of a stretch of empty segments, by about its cells: the
-// wave of the segment before it up to kGapWave, one workgroup up to kGapBlock,
-// and all workgroups of the last kernel beyond.  (Only the last kind is listed
-// with an atomic add on one counter: those cost 14 ns each, one after another.)
-constexpr uint32_t kGapWave = 4096, kGapBlock = 65536;
-GB_DEV uint32_t gap_segs(const SegCode& c, uint32_t cells) { return cells >> (c.wx + c.wy); }
 
 // A segment's place: its grid's outputs, its first cell and its cell count.
 struct SegPlace {
@@ -430,17 +476,21 @@ GB_DEV void write_gap(const FinishArgs& a, uint32_t s0, uint32_t s1, uint32_t p,
   }
 }
 
-// One wave: a stretch too long for one workgroup, listed for all of them.
-GB_DEV void list_gap(const FinishArgs& a, uint32_t s0, uint32_t s1, uint32_t p) {
+// One wave: what it leaves, listed as n tasks.
+GB_DEV void list_tasks(const FinishArgs& a, uint32_t what, uint32_t n) {
   if (lane_id() != 0) return;
-  const uint32_t at = atomicAdd(&a.ctl->ngaps, 1u);
-  if (at >= a.gap_cap) {
-    atomicOr(&a.ctl->error, kErrInternal);
-    return;
-  }
-  a.gaps[3 * at] = s0;
-  a.gaps[3 * at + 1] = s1;
-  a.gaps[3 * at + 2] = p;
+  const uint32_t l = blockIdx.x & (a.task_lists - 1);
+  const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(a.ntasks + l * kTaskStride),
+                                (1ull << 32) | n);
+  const uint32_t e = static_cast<uint32_t>(at >> 32);
+  if (e < a.task_cap) a.tasks[static_cast<uint64_t>(l) * a.task_cap + e] = make_uint2(what, static_cast<uint32_t>(at));
+  else atomicOr(&a.ctl->error, kErrInternal);
+}
+
+// A stretch of `segs` empty segments: nothing, or listed when it is more than its wave's.
+GB_DEV void list_gap(const FinishArgs& a, uint32_t what, uint32_t segs) {
+  const uint32_t per = gap_segs(a.code, kGapTask);
+  if (segs > gap_segs(a.code, kGapWave)) list_tasks(a, kTaskGap | what, segs / per + (segs % per ? 1u : 0u));
 }
 
 // A record as a segment's pairs see it: its cells inside the segment.
@@ -670,17 +720,23 @@ struct FinishLds {
   alignas(16) uint8_t d[Cap + 4];
 };
 
-// One list entry, one wave.
+// List entry j, one wave.
 template <uint32_t Cap, int Cells, bool Batched, bool Rows>
-GB_DEV void finish_segment(const FinishArgs& a, const SegEntry& e0, const SegEntry& e1, const RecordRun& run,
-                           FinishLds<Cap, Cells>& lds) {
+GB_DEV void finish_segment(const FinishArgs& a, uint32_t j, const SegEntry& e0, const SegEntry& e1, const RecordRun& run,
+                           uint32_t crowd, FinishLds<Cap, Cells>& lds) {
   constexpr int C = Cells / kWave;  // cells per lane
   static_assert(Cap % 4 == 0 && Cap > static_cast<uint32_t>(Cells), "differences fit the staging");
   const uint32_t lane = lane_id();
   const uint32_t seg = e0.seg, p0 = e0.pair, seg1 = e1.seg, p1 = e1.pair;
   if (seg1 - seg - 1 != 0 && seg1 - seg - 1 <= gap_segs(a.code, kGapWave)) write_gap<Batched>(a, seg + 1, seg1, p1, lane, kWave);
   const uint32_t n = p1 - p0;
-  if (n > Cap) return;  // a workgroup's
+  if (n > crowd) {  // workgroups': listed, and its groups' counts cleared for them
+    const uint32_t chunks = chunks_of(n);
+    uint32_t* g = a.groups + static_cast<uint64_t>(group_row_of(p0)) * row_cells(a.code);
+    for (uint32_t i = lane; i < groups_of(chunks) * row_cells(a.code); i += kWave) g[i] = 0;
+    list_tasks(a, j, chunks);
+    return;
+  }
   const SegPlace pl = seg_place<Batched>(a, seg);
   uint32_t* diff = lds.obj;
 #pragma unroll
@@ -755,7 +811,7 @@ __global__ __launch_bounds__(kWave, 4) void finish_kernel(FinishArgs a) {
   // entries j0 .. j0 + kFinishRun, one per lane (what lies past the list's end is not used)
   const SegEntry mine = a.list[j0 + lane < a.list_cap ? j0 + lane : a.list_cap];
   if (build_failed(a.ctl)) return;
-  const uint32_t nlist = a.ctl->nlist;
+  const uint32_t nlist = a.ctl->nlist, crowd = a.ctl->crowd < Cap ? a.ctl->crowd : Cap;
   auto entry = [&](uint32_t i) {
     SegEntry e;
     e.seg = wave_readlane(mine.seg, static_cast<int>(i));
@@ -768,7 +824,7 @@ __global__ __launch_bounds__(kWave, 4) void finish_kernel(FinishArgs a) {
     // the empty segments before the first listed one
     const uint32_t s1 = nlist ? entry(0).seg : a.code.nsegs;
     if (s1 > 0 && s1 <= gap_segs(a.code, kGapWave)) write_gap<Batched>(a, 0, s1, 0, lane, kWave);
-    else if (s1 > gap_segs(a.code, kGapBlock)) list_gap(a, 0, s1, 0);
+    else list_gap(a, kTaskFirst, s1);
   }
   if (j0 >= nlist) return;
   const uint32_t m = nlist - j0 < kFinishRun ? nlist - j0 : kFinishRun;
@@ -778,8 +834,8 @@ __global__ __launch_bounds__(kWave, 4) void finish_kernel(FinishArgs a) {
     const bool more = i + 1 < m;
     const SegEntry e2 = entry(more ? i + 2 : i + 1);
     const RecordRun next(a, e1.rec, e2.rec);  // (none when there is no next entry)
-    if (e1.seg - e0.seg - 1 > gap_segs(a.code, kGapBlock)) list_gap(a, e0.seg + 1, e1.seg, e1.pair);
-    finish_segment<Cap, Cells, Batched, Rows>(a, e0, e1, run, s_lds);
+    list_gap(a, j0 + i, e1.seg - e0.seg - 1);
+    finish_segment<Cap, Cells, Batched, Rows>(a, j0 + i, e0, e1, run, crowd, s_lds);
     if (!more) break;
     e0 = e1;
     e1 = e2;
@@ -788,125 +844,253 @@ __global__ __launch_bounds__(kWave, 4) void finish_kernel(FinishArgs a) {
   }
 }
 
-// What finish_kernel leaves: segments with more than `least` and at most `most`
-// pairs, one workgroup each, and longer stretches of empty segments.  Workgroup
-// b looks at every gridDim-th list entry from b, 64 at a time.  The records of
-// a segment are split into one run per wave; each wave counts its own run, the
-// counts are scanned over (cell, wave), and each wave places its run from its
-// own cursors.  Mid: this launch takes the stretches of up to kGapBlock cells;
-// Last: it takes the listed ones.
-template <int Block, uint32_t Cap, bool Mid, bool Last, bool Batched, bool Rows>
-__global__ __launch_bounds__(Block) void finish_big_kernel(FinishArgs a, uint32_t least, uint32_t most) {
-  constexpr int W = Block / kWave;
-  constexpr int kDiff = kSegCells + 4;
-  static_assert(Cap % 4 == 0 && Cap >= static_cast<uint32_t>(W * kDiff), "the waves' differences fit the staging");
-  __shared__ PlaceLds<kSegCells> s_place[W];
-  __shared__ __align__(16) uint32_t s_obj[Cap + 4];   // the waves' coverage differences first, then the staged pairs
-  __shared__ __align__(16) uint8_t s_d[Cap + 4];
-  __shared__ uint32_t s_wtot[W];
+// The tasks the waves listed, found by number: lane l holds list l's.
+struct TaskMap {
+  uint32_t entries, upto;   // the list's entries; tasks of this list and those before it
+  uint32_t total;
+};
+GB_DEV TaskMap task_map(const FinishArgs& a) {
+  const uint32_t lane = lane_id();
+  const uint64_t n = lane < a.task_lists ? a.ntasks[lane * kTaskStride] : 0;
+  TaskMap m;
+  m.entries = static_cast<uint32_t>(n >> 32);
+  m.upto = wave_inclusive(static_cast<uint32_t>(n), OpAdd{});
+  m.total = wave_readlane(m.upto, kWave - 1);
+  return m;
+}
+
+// Task t (below total): what it is of, and which of its tasks.  One whole wave;
+// a list's entries are in the order of their first tasks (one add gave both).
+GB_DEV uint32_t find_task(const FinishArgs& a, const TaskMap& m, uint32_t t, uint32_t& part) {
+  const uint32_t lane = lane_id();
+  const uint32_t l = static_cast<uint32_t>(__popcll(ballot(m.upto <= t)));  // (below total: some list's upto exceeds t)
+  if (l) t -= wave_readlane(m.upto, static_cast<int>(l - 1));
+  uint32_t lo = 0, end = wave_readlane(m.entries, static_cast<int>(l));
+  const uint2* e = a.tasks + static_cast<uint64_t>(l) * a.task_cap;
+  while (end - lo > 1) {
+    const uint32_t step = (end - lo + kWave - 1) / kWave;
+    const uint32_t g = lo + lane * step;
+    const uint32_t c = static_cast<uint32_t>(__popcll(ballot(g < end && e[g].y <= t)));
+    lo += (c - 1) * step;
+    end = lo + step < end ? lo + step : end;
+  }
+  part = t - __builtin_amdgcn_readfirstlane(e[lo].y);
+  return __builtin_amdgcn_readfirstlane(e[lo].x);
+}
+
+constexpr int kTaskBlock = 256;
+constexpr int kTaskWaves = kTaskBlock / kWave;
+constexpr uint32_t kTaskDiff = kSegCells + 4;   // a wave's coverage differences
+constexpr uint32_t kTaskCap = 2 * kChunkPairs;  // pairs a workgroup stages
+static_assert(kTaskBlock == kSegCells, "a thread per cell");
+
+// Records [r0, r1) of a chunk, one run per wave (of whole sixteens), counted into
+// the wave's coverage: diff[c] = the run's pairs in cell c.  The caller's barrier
+// follows before other waves' counts are read.
+template <bool Rows>
+GB_DEV RecordRun count_chunk(const FinishArgs& a, uint32_t r0, uint32_t r1, uint32_t width, uint32_t w, uint32_t* diff) {
+  const uint32_t lane = lane_id();
+  const uint64_t nr = r1 - r0;
+  const uint64_t per = (nr + kTaskWaves * 16 - 1) / (kTaskWaves * 16) * 16;
+  const uint32_t off0 = static_cast<uint32_t>(w * per < nr ? w * per : nr);
+  const uint32_t off1 = static_cast<uint32_t>(off0 + per < nr ? off0 + per : nr);
+  for (uint32_t c = lane; c < kTaskDiff; c += kWave) diff[c] = 0;
+  wave_sync();
+  const RecordRun run(a, r0 + off0, r0 + off1);
+  count_records<Rows>(a, run, width, diff);
+  wave_sync();
+  // coverage, four consecutive cells per lane
+  uint32_t* cur = diff + 4 * lane;
+  const uint32_t x0 = cur[0], x1 = x0 + cur[1], x2 = x1 + cur[2], x3 = x2 + cur[3];
+  const uint32_t ci = wave_inclusive(x3, OpAdd{}) - x3;
+  cur[0] = ci + x0;
+  cur[1] = ci + x1;
+  cur[2] = ci + x2;
+  cur[3] = ci + x3;
+  return run;
+}
+
+// First record of chunk c of a segment's `chunks`, of records [r0, r1).
+GB_DEV uint32_t chunk_first(uint32_t r0, uint32_t r1, uint32_t chunks, uint32_t c) {
+  const uint64_t nr = r1 - r0, per = (nr + chunks - 1) / chunks, off = per * c;
+  return r0 + static_cast<uint32_t>(off < nr ? off : nr);
+}
+
+// The pairs per cell of every chunk of the segments that have several.
+template <bool Batched, bool Rows>
+__global__ __launch_bounds__(kTaskBlock) void finish_count_kernel(FinishArgs a) {
+  __shared__ uint32_t s_diff[kTaskWaves * kTaskDiff];
   if (build_failed(a.ctl)) return;
-  const uint32_t nlist = a.ctl->nlist;
+  const TaskMap map = task_map(a);
+  const uint32_t tid = threadIdx.x;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  for (uint32_t t = blockIdx.x; t < map.total; t += gridDim.x) {
+    uint32_t chunk;
+    const uint32_t what = find_task(a, map, t, chunk);
+    if (what & kTaskGap) continue;
+    const SegEntry e0 = a.list[what], e1 = a.list[what + 1];
+    const uint32_t chunks = chunks_of(e1.pair - e0.pair);
+    if (chunks == 1) continue;
+    const SegPlace pl = seg_place<Batched>(a, e0.seg);
+    count_chunk<Rows>(a, chunk_first(e0.rec, e1.rec, chunks, chunk), chunk_first(e0.rec, e1.rec, chunks, chunk + 1), pl.width, w,
+                      s_diff + w * kTaskDiff);
+    __syncthreads();
+    uint32_t n = 0;
+#pragma unroll
+    for (int v = 0; v < kTaskWaves; ++v) n += s_diff[v * kTaskDiff + tid];
+    const uint32_t cells = row_cells(a.code);
+    if (tid < cells) {
+      a.rows[static_cast<uint64_t>(row_of(e0.pair) + chunk) * cells + tid] = n;
+      const uint32_t groups = groups_of(chunks);
+      if (groups && n) {
+        const uint32_t g = chunk / kGroupChunks < groups ? chunk / kGroupChunks : groups - 1;
+        atomicAdd(a.groups + static_cast<uint64_t>(group_row_of(e0.pair) + g) * cells + tid, n);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// The tasks: pieces of long stretches of empty segments, and the chunks of crowded
+// segments, each placed from where the chunks before it end in every cell.  A chunk
+// whose pairs exceed the staging (long records, or a segment of kMaxChunks) goes in
+// rounds of its records.  256 threads, so that four workgroups, at different phases,
+// share a CU's LDS.  Bound by the latency of those phases and, where thousands of
+// objects share a cell, by LDS atomics on the same words: 45M pairs crowded into an
+// eighth of their box 303 us (1024-thread workgroups, one a segment: 358), into a
+// millionth 347 (10883); mesh of 4.3M pairs 32 (57 and 34 for its larger segments).
+template <bool Batched, bool Rows>
+__global__ __launch_bounds__(kTaskBlock) void finish_tasks_kernel(FinishArgs a) {
+  __shared__ PlaceLds<kSegCells> s_place[kTaskWaves];
+  __shared__ __align__(16) uint32_t s_obj[kTaskCap + 4];   // the waves' coverage first, then the staged pairs
+  __shared__ __align__(16) uint8_t s_d[kTaskCap + 4];
+  __shared__ uint32_t s_at[kSegCells];                     // a cell's first pair of the round less its first slot
+  __shared__ uint32_t s_wtot[kTaskWaves];
+  static_assert(kTaskCap % 4 == 0 && kTaskCap >= kTaskWaves * kTaskDiff, "the waves' coverage fits the staging");
+  if (build_failed(a.ctl)) return;
+  const TaskMap map = task_map(a);
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  uint32_t* const diff = s_obj + w * kDiff;
-  if constexpr (Last) {
-    const uint32_t ngaps = a.ctl->ngaps;
-    for (uint32_t i = 0; i < ngaps; ++i)
-      write_gap<Batched>(a, a.gaps[3 * i], a.gaps[3 * i + 1], a.gaps[3 * i + 2],
-                         static_cast<uint64_t>(blockIdx.x) * Block + tid, static_cast<uint64_t>(gridDim.x) * Block);
-  }
-  if (Mid && blockIdx.x == 0) {
-    const uint32_t s1 = nlist ? a.list[0].seg : a.code.nsegs;
-    if (s1 > gap_segs(a.code, kGapWave) && s1 <= gap_segs(a.code, kGapBlock)) write_gap<Batched>(a, 0, s1, 0, tid, Block);
-  }
-  for (uint64_t j0 = blockIdx.x; j0 < nlist; j0 += static_cast<uint64_t>(gridDim.x) * kWave) {
-   // every wave finds the same entries
-   const uint64_t jl = j0 + static_cast<uint64_t>(lane) * gridDim.x;
-   bool mine = false;
-   if (jl < nlist) {
-     const SegEntry e0 = a.list[jl], e1 = a.list[jl + 1];
-     const uint32_t n = e1.pair - e0.pair, gap = e1.seg - e0.seg - 1;
-     mine = (n > least && n <= most) ||
-            (Mid && gap > gap_segs(a.code, kGapWave) && gap <= gap_segs(a.code, kGapBlock));
-   }
-   uint64_t todo = ballot(mine);
-   while (todo) {
-    const uint32_t j = static_cast<uint32_t>(j0 + static_cast<uint64_t>(__builtin_ctzll(todo)) * gridDim.x);
-    todo &= todo - 1;
-    const SegEntry e0 = a.list[j], e1 = a.list[j + 1];
-    const uint32_t r0 = e0.rec, r1 = e1.rec, p0 = e0.pair, n = e1.pair - p0;
-    if constexpr (Mid) {
-      const uint32_t gap = e1.seg - e0.seg - 1;
-      if (gap > gap_segs(a.code, kGapWave) && gap <= gap_segs(a.code, kGapBlock))
-        write_gap<Batched>(a, e0.seg + 1, e1.seg, e1.pair, tid, Block);
+  uint32_t* const diff = s_obj + w * kTaskDiff;
+  for (uint32_t t = blockIdx.x; t < map.total; t += gridDim.x) {
+    uint32_t part;
+    const uint32_t what = find_task(a, map, t, part);
+    if (what & kTaskGap) {
+      const uint32_t j = what & ~kTaskGap, nlist = a.ctl->nlist;
+      const uint32_t s0 = j == kTaskFirst ? 0u : a.list[j].seg + 1;
+      const uint32_t next = j == kTaskFirst ? 0u : j + 1;
+      const uint32_t s1 = nlist ? a.list[next].seg : a.code.nsegs;  // (entry nlist closes the list)
+      const uint32_t p = j == kTaskFirst ? 0u : a.list[next].pair;
+      const uint32_t per = gap_segs(a.code, kGapTask);
+      const uint32_t b = s0 + part * per;
+      write_gap<Batched>(a, b, s1 - b < per ? s1 : b + per, p, tid, kTaskBlock);
+      continue;
     }
-    if (n <= least || n > most) continue;
+    const SegEntry e0 = a.list[what], e1 = a.list[what + 1];
+    const uint32_t p0 = e0.pair, n = e1.pair - p0;
+    const uint32_t chunks = chunks_of(n);
     const SegPlace pl = seg_place<Batched>(a, e0.seg);
-    const uint64_t nr = r1 - r0;
-    const uint64_t per = (nr + W * kWave - 1) / (W * kWave) * kWave;
-    const uint32_t off0 = static_cast<uint32_t>(w * per < nr ? w * per : nr);
-    const uint32_t off1 = static_cast<uint32_t>(off0 + per < nr ? off0 + per : nr);
-    for (uint32_t c = lane; c < kDiff; c += kWave) diff[c] = 0;
-    wave_sync();
-    const RecordRun run(a, r0 + off0, r0 + off1);
-    count_records<Rows>(a, run, pl.width, diff);
-    wave_sync();
-    {
-      // the wave's coverage, four consecutive cells per lane
-      uint32_t* cur = diff + 4 * lane;
-      const uint32_t x0 = cur[0], x1 = x0 + cur[1], x2 = x1 + cur[2], x3 = x2 + cur[3];
-      const uint32_t ci = wave_inclusive(x3, OpAdd{}) - x3;
-      cur[0] = ci + x0;
-      cur[1] = ci + x1;
-      cur[2] = ci + x2;
-      cur[3] = ci + x3;
-    }
-    __syncthreads();
-    uint32_t cnt = 0;
-    if (tid < kSegCells) {
-      for (int v = 0; v < W; ++v) cnt += s_obj[v * kDiff + tid];
-    }
-    uint32_t tot;
-    const uint32_t begin = block_exclusive_sum<Block>(cnt, s_wtot, tot);
     const uint64_t lp = p0 - pl.pair_base;
-    if (tid < kSegCells) {
-      uint32_t c = begin;
-      for (int v = 0; v < W; ++v) {
-        const uint32_t x = s_obj[v * kDiff + tid];
-        s_obj[v * kDiff + tid] = c;
+    uint32_t* const ranges = pl.ranges + 2 * (static_cast<uint64_t>(pl.cell0) + tid);
+    uint32_t r0 = chunk_first(e0.rec, e1.rec, chunks, part);
+    const uint32_t r1 = chunk_first(e0.rec, e1.rec, chunks, part + 1);
+    uint32_t rounds = 1, at = 0;   // at: the cell's next pair in the segment
+    if (chunks > 1) {
+      // the cell's pairs in this chunk, in those before it, and in all of them
+      const uint32_t cells = row_cells(a.code), groups = groups_of(chunks);
+      const uint32_t mine = groups == 0 ? 0u : part / kGroupChunks < groups ? part / kGroupChunks : groups - 1;
+      uint32_t before = 0, total = 0, own = 0;
+      if (tid < cells) {
+        const uint32_t* row = a.rows + static_cast<uint64_t>(row_of(p0)) * cells + tid;
+        own = row[static_cast<uint64_t>(part) * cells];
+        if (groups) {
+          const uint32_t* g = a.groups + static_cast<uint64_t>(group_row_of(p0)) * cells + tid;
+#pragma unroll 8
+          for (uint32_t i = 0; i < groups; ++i) {
+            const uint32_t x = g[static_cast<uint64_t>(i) * cells];
+            total += x;
+            before += i < mine ? x : 0u;
+          }
+#pragma unroll 8
+          for (uint32_t i = mine * kGroupChunks; i < part; ++i) before += row[static_cast<uint64_t>(i) * cells];
+        } else {
+#pragma unroll 8
+          for (uint32_t i = 0; i < chunks; ++i) {
+            const uint32_t x = row[static_cast<uint64_t>(i) * cells];
+            total += x;
+            before += i < part ? x : 0u;
+          }
+        }
+      }
+      uint32_t sum;
+      const uint32_t begin = block_exclusive_sum<kTaskBlock>(total, s_wtot, sum);
+      if (part == 0 && tid < pl.ncell) {
+        ranges[0] = static_cast<uint32_t>(lp) + begin;
+        ranges[1] = static_cast<uint32_t>(lp) + begin + total;
+      }
+      at = begin + before;
+      block_exclusive_sum<kTaskBlock>(own, s_wtot, sum);
+      if (sum > kTaskCap) rounds = (sum + kChunkPairs - 1) / kChunkPairs;
+    }
+    const uint32_t per = static_cast<uint32_t>((static_cast<uint64_t>(r1 - r0) + rounds - 1) / rounds);
+    uint32_t* const oc = pl.cells + lp;
+    uint32_t* const oo = pl.objs + lp;
+    do {  // (a chunk of no records is one empty round)
+      const uint32_t re = r1 - r0 < per ? r1 : r0 + per;
+      const RecordRun run = count_chunk<Rows>(a, r0, re, pl.width, w, diff);
+      __syncthreads();
+      uint32_t cnt = 0;
+#pragma unroll
+      for (int v = 0; v < kTaskWaves; ++v) cnt += s_obj[v * kTaskDiff + tid];
+      uint32_t m;
+      const uint32_t begin = block_exclusive_sum<kTaskBlock>(cnt, s_wtot, m);
+      const bool staged = m <= kTaskCap;
+      uint32_t c = staged ? begin : at;
+#pragma unroll
+      for (int v = 0; v < kTaskWaves; ++v) {
+        const uint32_t x = s_obj[v * kTaskDiff + tid];
+        s_obj[v * kTaskDiff + tid] = c;
         c += x;
       }
-      if (tid < pl.ncell) {
-        uint32_t* rg = pl.ranges + 2 * (static_cast<uint64_t>(pl.cell0) + tid);
-        rg[0] = static_cast<uint32_t>(lp) + begin;
-        rg[1] = static_cast<uint32_t>(lp) + begin + cnt;
+      if (chunks == 1 && tid < pl.ncell) {
+        ranges[0] = static_cast<uint32_t>(lp) + begin;
+        ranges[1] = static_cast<uint32_t>(lp) + begin + cnt;
       }
-    }
-    __syncthreads();
-    uint32_t cur[kSegCells / kWave];
-#pragma unroll
-    for (int k = 0; k < kSegCells / kWave; ++k) cur[k] = diff[kSegCells / kWave * lane + k];
-    __syncthreads();
-    uint32_t* oc = pl.cells + lp;
-    uint32_t* oo = pl.objs + lp;
-    if (n <= Cap) {
-      place_records<Rows>(a, run, pl.width, cur, s_place[w], [&](bool in, uint32_t pos, uint32_t d, uint32_t obj) {
-        const uint32_t p = in ? pos : Cap;
-        s_obj[p] = obj;
-        s_d[p] = static_cast<uint8_t>(d);
-      });
+      s_at[tid] = at - begin;
+      at += cnt;
       __syncthreads();
-      store_staged(oc, oo, s_obj, s_d, pl.cell0, n, tid, Block);
-    } else {
-      place_records<Rows>(a, run, pl.width, cur, s_place[w], [&](bool in, uint32_t pos, uint32_t d, uint32_t obj) {
-        if (in) {
-          oc[pos] = pl.cell0 + d;
-          oo[pos] = obj;
+      uint32_t cur[kSegCells / kWave];
+#pragma unroll
+      for (int k = 0; k < kSegCells / kWave; ++k) cur[k] = diff[kSegCells / kWave * lane + k];
+      __syncthreads();
+      if (staged) {
+        place_records<Rows>(a, run, pl.width, cur, s_place[w], [&](bool in, uint32_t pos, uint32_t d, uint32_t obj) {
+          const uint32_t p = in ? pos : kTaskCap;
+          s_obj[p] = obj;
+          s_d[p] = static_cast<uint8_t>(d);
+        });
+        __syncthreads();
+        if (chunks == 1) {
+          store_staged(oc, oo, s_obj, s_d, pl.cell0, n, tid, kTaskBlock);
+        } else {
+          for (uint32_t i = tid; i < m; i += kTaskBlock) {
+            const uint32_t d = s_d[i];
+            const uint32_t p = s_at[d] + i;
+            oc[p] = pl.cell0 + d;
+            oo[p] = s_obj[i];
+          }
         }
-      });
-    }
-    __syncthreads();
-   }
+      } else {
+        place_records<Rows>(a, run, pl.width, cur, s_place[w], [&](bool in, uint32_t pos, uint32_t d, uint32_t obj) {
+          if (in) {
+            oc[pos] = pl.cell0 + d;
+            oo[pos] = obj;
+          }
+        });
+      }
+      __syncthreads();
+      r0 = re;
+    } while (r0 < r1);
   }
 }
 
