@@ -505,13 +505,14 @@ void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint
   if (b.ntris == 0 || cap == 0) return;
   RecordPlan rp{};
   Layout L{};
-  // a workspace too small for the list of segments: wider segments, fewer of them
+  // a workspace too small for the list of segments, or more of them than a launch of
+  // a wave per kFinishRun takes (2^32 - 1 threads): wider segments, fewer of them
   for (uint32_t wider = 0;; ++wider) {
     if (!plan_records(grids, ngrids, cells, pairs, wider, b.culled, &rp)) return;
     const int pp = b.plan.sp.passes, rpp = rp.plan.sp.passes;
     if (!(b.culled ? cull_records_pay(cap, b.ntris, pp, rpp) : records_pay(pairs, b.ntris, pp, rpp))) return;
     L = make_record_layout(b.ntris, cap, rp, ngrids, b.batched, b.culled);
-    if (L.total <= ws_bytes) break;
+    if (L.total <= ws_bytes && ceil_div(L.list_cap, kFinishRun) * kWave <= 0xFFFFFFFFull) break;
   }
   b.rec = true;
   b.code = rp.code;

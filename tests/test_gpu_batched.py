@@ -182,3 +182,40 @@ def test_batched_build_object_repeats(G):
             assert torch.equal(o.ranges, r.ranges)
     for o, s in zip(outs, batch):
         _cmp_oracle(o, s)
+
+
+def test_batch_of_more_segments_than_a_launch_takes(G):
+    # 131072 columns of 1024 cells: a wave per two cells would be 2^32 threads, one more than a launch holds.
+    # Every grid is the same scene, so every grid's outputs are the first one's, and that one the oracle's
+    n = 1 << 17
+    rng = np.random.default_rng(6)
+    z = np.concatenate([np.arange(0, 1024, 8), rng.integers(0, 1000, 12)]).astype(np.float64)
+    a = np.column_stack([np.full((len(z), 2), 0.3), z + 0.25])
+    b = a + [0.2, 0.2, 8.0]
+    verts, tris = scenes.soup_from_vertices(np.stack([a, b, b], 1))
+    s = scenes.Scene("column", verts, tris, np.zeros(3, np.float32), np.asarray([1, 1, 1024], np.float32),
+                     np.asarray([1, 1, 1024], np.uint32))
+    oc, oo, orr = oracle.build_scene(s)
+    k = len(oc)
+    assert k * n > 1 << 27 and k > 4 * s.ntris
+    g = G.GridInput.from_scene(s)
+    cells, objs = (torch.empty((n, k), dtype=torch.int32, device="cuda") for _ in range(2))
+    ranges = torch.empty((n, 2048), dtype=torch.int32, device="cuda")
+    arr = (G.grid_desc * n)()
+    v = G._desc_view(arr)
+    one = G._descs([g])[0]
+    v["verts_soa"], v["tris"], v["nverts"], v["ntris"] = one.verts_soa, one.tris, one.nverts, one.ntris
+    v["lo"], v["hi"], v["res"] = list(one.lo), list(one.hi), list(one.res)
+    at = np.arange(n, dtype=np.uint64)
+    v["cells"], v["objs"] = cells.data_ptr() + at * np.uint64(4 * k), objs.data_ptr() + at * np.uint64(4 * k)
+    v["ranges"], v["cap_pairs"] = ranges.data_ptr() + at * np.uint64(4 * 2048), k
+    L = G.lib()
+    ws = G.Workspace()
+    need = int(L.grid_workspace_size_batched(arr, n))
+    wp, wn = ws.ptr_size(need + (4 << 30))   # with room for the list of segments
+    _say("batch of", n, "columns", n * k, "pairs, workspace", need)
+    assert L.grid_build_batched(arr, n, wp, wn, G._stream()) == G.GRID_OK
+    assert bool((torch.from_numpy(v["npairs"].astype(np.int64)) == k).all())
+    for t, o in ((cells, oc), (objs, oo), (ranges, orr)):
+        assert np.array_equal(t[0].cpu().numpy().view(np.uint32), o)
+        assert bool((t == t[0]).all())
