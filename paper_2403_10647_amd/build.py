@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgridbuild.so")
 SOURCES = ["gridbuild.hip"]
 HEADERS = ["common.hpp", "grid.hpp", "tiles.hpp", "kernels.hpp", "sort.hpp", "ranges.hpp", "records.hpp", "scan.hpp", "cull.hpp",
-           "compact.hpp", "raycast.hpp"]
+           "compact.hpp", "walk.hpp", "raycast.hpp"]
 ARCH = os.environ.get("GRIDBUILD_ARCH", "gfx950")
 
 FLAGS = [

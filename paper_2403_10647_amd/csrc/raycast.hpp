@@ -22,6 +22,7 @@
 #pragma once
 
 #include "grid.hpp"
+#include "walk.hpp"
 
 namespace gb {
 
@@ -86,10 +87,10 @@ struct RaycastArgs {
 // per lane.  What bounds it then: a turn is a chain of four dependent loads (a
 // cell's range, an object's id, its vertex indices, its vertices), and nearly
 // all of them miss L2, 73M sectors of 64 bytes for the case below; more waves
-// per SIMD are no faster (5 at 90 VGPRs: 2075 us, 6 at 79: 2196).  So the ranges
+// per SIMD are no faster (5 at 85 VGPRs: 2075 us, 6 at 79: 2196).  So the ranges
 // of several cells are loaded together, past the cell that will turn out to hold
 // the hit: 1, 2, 4, 6, 8 cells 2633, 2281, 2075, 2217, 2354 us.  1M rays over the
-// 10M-triangle arch grid: a ray per lane 4035 us, this 2114; 300k rays over a 1M
+// 10M-triangle arch grid: a ray per lane 4035 us, this 2132; 300k rays over a 1M
 // mesh 5906 and 674; 2000 over 5k uniform triangles 244 and 85.  Taking new rays
 // for lanes that are done gave nothing (2% slower at 140 rays a wave).
 constexpr int kRayCells = 4;
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(kWave, 4) void raycast_kernel(RaycastArgs a) {
   bool have = false;           // the lane's ray is being cast
   float t0 = 0.0f, t1 = a.tmax;
   int m = 0, k = 0, kend = 0;  // dominant axis, slab, last slab
-  float om = 0, dm = 1, o1 = 0, d1 = 0, o2 = 0, d2 = 0, w = 0, wt = 0, inv_dm = 0;
+  float om = 0, dm = 1, o1 = 0, d1 = 0, o2 = 0, d2 = 0, w = 0, wt = 0;
   float te = -__builtin_inff(), tdone = 0;         // far face of the slab, and of the one before
   int lo1 = 0, hi1 = 0, j1 = 0, hi2 = -1, j2 = 0;  // the slab's cells still to visit: j2 > hi2 when none are left
   if (r < a.nrays) {
@@ -158,7 +159,6 @@ __global__ __launch_bounds__(kWave, 4) void raycast_kernel(RaycastArgs a) {
       const float lom = axis_of(G.lo, m), inv = axis_of(G.inv, m), rm = axis_of(fres, m) - 1.0f;
       w = __fdiv_rn(__fsub_rn(axis_of(a.hi, m), lom), axis_of(fres, m));  // slab width
       wt = fabsf(w / dm);                                                  // in t
-      inv_dm = 1.0f / dm;
       const float step = dm > 0.0f ? 1.0f : -1.0f;
       const float k0 = fminf(fmaxf(floorf((om + t0 * dm - lom) * inv), 0.0f), rm);
       const float k1 = fminf(fmaxf(floorf((om + t1 * dm - lom) * inv), 0.0f), rm);
@@ -203,11 +203,8 @@ __global__ __launch_bounds__(kWave, 4) void raycast_kernel(RaycastArgs a) {
         if (j2 > hi2 && (up ? k < kend : k > kend)) {
           k += up ? 1 : -1;
           const float pa = axis_of(G.lo, m) + static_cast<float>(k) * w;
-          float ta = (pa - om) * inv_dm, tb = (pa + w - om) * inv_dm;
-          if (!(fabsf(inv_dm) < 1e30f)) {  // (0 * inf)
-            ta = (pa - om) / dm;
-            tb = (pa + w - om) / dm;
-          }
+          float ta, tb;
+          slab_faces(pa, w, om, dm, ta, tb);
           tdone = te;
           te = fmaxf(ta, tb);
           const float ps = fmaxf(t0, fminf(ta, tb) - kWalkPad * wt);

@@ -125,3 +125,23 @@ def test_raycast_turns(G, nrays, n, res):
     ot, oo = oracle.raycast(s.verts, s.tris, s.lo, s.hi, rays, float("inf"))
     assert np.array_equal(ho.cpu().numpy().view(np.uint32), oo)
     assert np.array_equal(ht.cpu().numpy().view(np.uint32), ot.view(np.uint32))
+
+
+@pytest.mark.parametrize("far", [30.0, 1000.0])
+def test_raycast_from_far_away(G, far):
+    """Origins thousands and tens of thousands of cells from the box, aimed at points in it."""
+    s = scenes.make_scene("uniform", seed=7, ntris=20_000)
+    rng = np.random.default_rng(int(far))
+    n = 2000
+    lo, hi = s.lo.astype(np.float64), s.hi.astype(np.float64)
+    u = rng.normal(size=(n, 3))
+    o = (lo + hi) / 2 + u / np.linalg.norm(u, axis=1)[:, None] * np.linalg.norm(hi - lo) * far
+    d = lo + rng.uniform(0.0, 1.0, (n, 3)) * (hi - lo) - o
+    rays = np.ascontiguousarray(np.concatenate([o.T, d.T]), np.float32)
+    _say("raycast from", far, "boxes away, res", list(map(int, s.res)))
+    g = G.GridInput.from_scene(s)
+    ht, ho = G.raycast(g, G.build(g), torch.from_numpy(rays).cuda())
+    ot, oo = oracle.raycast(s.verts, s.tris, s.lo, s.hi, rays)
+    assert int((oo != 0xFFFFFFFF).sum()) > n // 20
+    assert np.array_equal(ho.cpu().numpy().view(np.uint32), oo)
+    assert np.array_equal(ht.cpu().numpy().view(np.uint32), ot.view(np.uint32))

@@ -63,3 +63,15 @@ def test_tile_owner_index_logic_on_the_host():
            f"-I{os.path.join(ROOT, 'paper_2403_10647_amd', 'csrc')}", os.path.join(SAN, "check_tile_owners.cpp"), "-o", exe]
     subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
     _run(exe)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_slab_faces_round_twice_on_the_host():
+    os.makedirs(OUT, exist_ok=True)
+    exe = os.path.join(OUT, "check_slab_faces")
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-ffp-contract=off",
+           "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
+           "-Xarch_host", "-fno-sanitize-recover=all",
+           f"-I{os.path.join(ROOT, 'paper_2403_10647_amd', 'csrc')}", os.path.join(SAN, "check_slab_faces.cpp"), "-o", exe]
+    subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
+    _run(exe)
