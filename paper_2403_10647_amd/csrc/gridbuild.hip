@@ -464,9 +464,9 @@ struct Build {
   uint64_t rec_cap = 0;   // ... and the launches' pair capacity
 };
 
-// Whether a sorted build under the current knobs may run by records: the knobs
-// that choose another pair generation are about the pairs themselves.
-bool records_allowed() { return g_build_path == 0 && !g_fused_expand && !g_per_object_pairs; }
+// Whether a plain sorted build under the current knobs may run by records: the
+// knobs that choose another pair generation are about the pairs themselves.
+bool records_allowed() { return !g_fused_expand && !g_per_object_pairs; }
 
 // Where a build by records is the faster one.  A box of one or two cells is about
 // as many records as pairs, and the records' extra steps then cost more than
@@ -1358,7 +1358,8 @@ int build_plain(const float* verts_soa, uint32_t nverts, const uint32_t* tris, u
   int st = prepare_plain(b, verts_soa, nverts, tris, ntris, lo, hi, res, ws, ws_bytes, out->cap_pairs, stream);
   if (st) return st;
   b.no_alloc = no_alloc;
-  if (records_allowed())
+  int path = g_build_path;
+  if (path == 0 && records_allowed())
     try_records(b, &b.gs.one, 1, ncells_of(res), out->cap_pairs, out->cap_pairs, ws_bytes);
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
@@ -1368,7 +1369,6 @@ int build_plain(const float* verts_soa, uint32_t nverts, const uint32_t* tris, u
   if ((st = launch_zero(b.ws, b.L.zero_end, b.s))) return st;
   if ((st = launch_count<false>(b))) return st;
   if ((st = launch_plan<false>(b))) return st;
-  int path = g_build_path;
   if (path == 2) {
     // the statistics pass: the count's totals, read back once, choose the path
     Control c;
@@ -1418,7 +1418,7 @@ int grid_build_culled(const float* verts_soa, uint32_t nverts, const uint32_t* t
   if (st) return st;
   b.culled = true;
   b.out_cap = out->cap_pairs;
-  if (records_allowed() && out->cap_pairs > 0)
+  if (out->cap_pairs > 0)
     // (outputs may be sized for the box pairs: segments as for eight kept pairs a cell at most, since a
     // narrower segment is more records for the same rows: 1M hairball-like 3940 us at four cells)
     try_records(b, &b.gs.one, 1, ncells_of(res), box_cap, std::min({box_cap, out->cap_pairs, 8 * ncells_of(res)}), ws_bytes);

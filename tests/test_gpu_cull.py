@@ -189,3 +189,20 @@ def test_culled_short_boxes_test_pairs(G):
         k = G.trace_read()
         G.trace_enable(False)
     assert 5 * nbox < 12 * s.ntris and "cull_rows" not in k, (nbox, sorted(k))
+
+
+@pytest.mark.parametrize("knob,val", [("build_path", 1), ("build_path", 2), ("per_object_pairs", 1), ("fused_expand", 1)])
+def test_plain_builds_knobs_leave_culled_rows(G, knob, val):
+    # knobs about plain builds' pairs do not take a culled build off its rows
+    verts, tris = scenes.soup_from_vertices(_axis_cases(np.random.default_rng(9), 2001, (96, 96, 96)))
+    s = _scene(verts, tris, [0, 0, 0], (96, 96, 96), (96, 96, 96), name=f"rows-{knob}{val}")
+    G.tune_set(knob, val)
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        _, nbox = _check(G, s)
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+        G.tune_set(knob, 0)
+    assert nbox >= 1 << 22 and "cull_rows" in k, (nbox, sorted(k))
