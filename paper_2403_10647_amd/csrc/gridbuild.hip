@@ -568,6 +568,15 @@ int launch_plan(Build& b) {
   return GRID_OK;
 }
 
+// The start of a build: its control block cleared, its count and its plan.
+template <bool B>
+int launch_counts(Build& b) {
+  int st = launch_zero(b.ws, b.L.zero_end, b.s);
+  if (st) return st;
+  if ((st = launch_count<B>(b))) return st;
+  return launch_plan<B>(b);
+}
+
 ExpandArgs expand_args(const Build& b) {
   ExpandArgs e{};
   e.gs = b.gs;
@@ -1359,22 +1368,30 @@ int build_plain(const float* verts_soa, uint32_t nverts, const uint32_t* tris, u
   if (st) return st;
   b.no_alloc = no_alloc;
   int path = g_build_path;
-  if (path == 0 && records_allowed())
+  const Plan pair_plan = b.plan;
+  const Layout pair_layout = b.L;
+  // (path 2 mostly takes the compact path up to kCompactMaxPairs, which needs the pairs' count)
+  if ((path == 0 || (path == 2 && out->cap_pairs > kCompactMaxPairs)) && records_allowed())
     try_records(b, &b.gs.one, 1, ncells_of(res), out->cap_pairs, out->cap_pairs, ws_bytes);
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
   b.gs.one.out_ranges = out->ranges;
   // the capacity bounds every launch; the kernels read the real NO on the device
   const uint64_t cap = out->cap_pairs;
-  if ((st = launch_zero(b.ws, b.L.zero_end, b.s))) return st;
-  if ((st = launch_count<false>(b))) return st;
-  if ((st = launch_plan<false>(b))) return st;
+  if ((st = launch_counts<false>(b))) return st;
   if (path == 2) {
     // the statistics pass: the count's totals, read back once, choose the path
     Control c;
     GB_TRY(hipMemcpyAsync(&c, at<Control>(b.ws, b.L.ctl), sizeof(Control), hipMemcpyDeviceToHost, b.s));
     GB_TRY(hipStreamSynchronize(b.s));
     path = choose_path(c.npairs, ncells_of(res));
+    if (b.rec && (path == 1 || !records_pay(c.npairs, ntris, pair_plan.sp.passes, b.plan.sp.passes))) {
+      // far fewer pairs than the capacity said: counted again, as pairs
+      b.rec = false;
+      b.plan = pair_plan;
+      b.L = pair_layout;
+      if ((st = launch_counts<false>(b))) return st;
+    }
   }
   g_last_path = path;
   if (path == 1) {
@@ -1425,9 +1442,7 @@ int grid_build_culled(const float* verts_soa, uint32_t nverts, const uint32_t* t
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
   b.gs.one.out_ranges = out->ranges;
-  if ((st = launch_zero(b.ws, b.L.zero_end, b.s))) return st;
-  if ((st = launch_count<false>(b))) return st;
-  if ((st = launch_plan<false>(b))) return st;  // checks the box pairs against box_cap
+  if ((st = launch_counts<false>(b))) return st;  // (the plan checks the box pairs against box_cap)
   if (b.rec) {
     if ((st = launch_records<false>(b, out->cells, out->objs, box_cap))) return st;
   } else if (b.plan.sp.passes == 0 || box_cap == 0) {
@@ -1652,10 +1667,8 @@ int prepare_batched(Build& b, BatchSetup& bs, const grid_desc* grids, uint32_t n
 }
 
 int count_phase_batched(Build& b, uint32_t ngrids, std::vector<uint64_t>& npairs, HostCtl* h) {
-  int st = launch_zero(b.ws, b.L.zero_end, b.s);
+  int st = launch_counts<true>(b);
   if (st) return st;
-  if ((st = launch_count<true>(b))) return st;
-  if ((st = launch_plan<true>(b))) return st;
   npairs.resize(ngrids);
   GB_TRY(hipMemcpyAsync(npairs.data(), at<uint64_t>(b.ws, b.L.npairs_out), ngrids * 8, hipMemcpyDeviceToHost, b.s));
   if ((st = read_ctl(b, h))) return st;
@@ -2041,9 +2054,7 @@ int grid_build_batched_async(const grid_desc* grids, uint32_t ngrids, void* ws, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   int st = prepare_batched(b, bs, grids, ngrids, ws, ws_bytes, s, true, host_staging, staging_bytes);
   if (st) return st;
-  if ((st = launch_zero(b.ws, b.L.zero_end, s))) return st;
-  if ((st = launch_count<true>(b))) return st;
-  if ((st = launch_plan<true>(b))) return st;
+  if ((st = launch_counts<true>(b))) return st;
   // sizes on the host are the capacities; the kernels read the true counts
   if (b.rec) return launch_records<true>(b, nullptr, nullptr, bs.cap);
   if (bs.cap > 0) {
@@ -2066,9 +2077,7 @@ int grid_count_batched_async(const grid_desc* grids, uint32_t ngrids, void* ws, 
   int st = prepare_batched(b, bs, grids, ngrids, ws, ws_bytes, s, false, host_staging, half, kCapFromWorkspace);
   if (st) return st;
   if (pair_cap) *pair_cap = b.layout_cap;
-  if ((st = launch_zero(b.ws, b.L.zero_end, s))) return st;
-  if ((st = launch_count<true>(b))) return st;
-  if ((st = launch_plan<true>(b))) return st;
+  if ((st = launch_counts<true>(b))) return st;
   GB_TRY(hipMemcpyAsync(counts_host, at<uint64_t>(b.ws, b.L.npairs_out), (ngrids + 1) * sizeof(uint64_t),
                         hipMemcpyDeviceToHost, s));
   return GRID_OK;

@@ -154,3 +154,25 @@ def test_few_pairs_a_triangle_sort_pairs(G):
     lo, hi = _random(rng, 160_000, res, (5, 3, 2))
     _build(G, _boxes(lo, hi, res, "boxes"), by_records=True)
     _build(G, _boxes(lo[:40_000], hi[:40_000], res, "fewer boxes"), by_records=False)
+
+
+@pytest.mark.parametrize("n,over,route", [(200_000, 1, "records"), (200_000, 5, "records"), (150_000, 30, "pairs"), (4000, 100, "compact")])
+def test_statistics_choose_among_all_paths(G, n, over, route):
+    # build_path 2: by records where the count bears them out, whatever the capacity says
+    s = scenes.make_scene("mixed" if route == "records" else "uniform", seed=3, ntris=n)
+    g = G.GridInput.from_scene(s)
+    no, _ = G.count(g)
+    print("statistics", n, no, over, flush=True)
+    G.tune_set("build_path", 2)
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        r = G.build(g, cap_pairs=no * over)
+        last = G.tune_get("last_path")
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+        G.tune_set("build_path", 0)
+    assert last == (1 if route == "compact" else 0)
+    assert ("finish" in k) == (route == "records") and ("compact_scan" in k) == (route == "compact"), sorted(k)
+    _same(r, s)
