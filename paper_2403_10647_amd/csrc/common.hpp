@@ -32,6 +32,8 @@ struct Control {
   uint64_t nitems;             // record builds: records of the build (npairs is then the pairs they hold)
   uint32_t nlist;              // record builds: segments that hold a record
   uint32_t crowd;              // record builds: pairs above which a segment is not its wave's alone
+  uint32_t rec_work_n;         // batches counted both ways: tile-owner runs of the records left for the plan kernel
+  uint32_t pad;
 };
 constexpr uint32_t kErrBadIndex = 1u;
 constexpr uint32_t kErrInternal = 2u;  // an internal consistency check failed (the build's output is invalid)

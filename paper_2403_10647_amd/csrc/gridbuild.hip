@@ -203,6 +203,7 @@ Plan make_plan(uint32_t bits, int max_digit = -1) {
 struct Layout {
   size_t ctl, hist, count_status, cull_status, cell_status, zero_end;
   size_t grid_pairs, list_status, ntasks, list, tasks, rows, groups;  // record builds
+  size_t rec_status, zero2, zero2_end;                                // ... of a batch counted both ways
   size_t start, box, tfo, tfg, tfo_work, cull_rec, sort_status, keys_alt, vals_alt, keys_alt2, vals_alt2, run, npairs_out, splits,
       tile_grid, table, sink, kmap, ksink, total;
   uint32_t ntfo, ncount_tiles, nsort_tiles_cap, nmerge_tiles_cap;
@@ -328,6 +329,37 @@ bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pair
   return true;
 }
 
+// The lists and tables of a build by records that come after its records: their
+// sizes, and the bytes the radix passes' look-back words share with those that are
+// written once the passes are done (rows only where a segment can hold several
+// chunks).  Lists of tasks: a wave adds at most four entries (and the first one
+// more), and there are no more crowded segments and long stretches than pairs and
+// segments allow.
+struct RecordSizes {
+  size_t list, list_status, ntasks, shared, rows_at, groups_at;
+};
+RecordSizes record_sizes(uint64_t cap_pairs, const RecordPlan& rp, Layout& L) {
+  const uint32_t bits = rp.code.wx + rp.code.wy;
+  L.list_cap = static_cast<uint32_t>(std::min<uint64_t>(rp.code.nsegs, cap_pairs));
+  const uint32_t blocks = static_cast<uint32_t>(ceil_div(L.list_cap, kFinishRun));
+  L.task_lists = 1;
+  while (L.task_lists < kTaskLists && L.task_lists * 128 < blocks) L.task_lists *= 2;
+  L.task_cap = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(blocks, L.task_lists) * 4 + 1,
+                                                        cap_pairs / kCrowdLeast + rp.code.nsegs / (kGapWave >> bits) + 2));
+  const uint64_t chunks = cap_pairs < 2 * kChunkPairs ? 0 : ceil_div(cap_pairs, kChunkPairs);
+  const uint64_t groups = chunks < 2 * kGroupChunks ? 0 : ceil_div(chunks, kGroupChunks);
+  RecordSizes z{};
+  z.list = (static_cast<size_t>(L.list_cap) + 1) * sizeof(SegEntry);
+  z.list_status = (ceil_div(cap_pairs, kSegListTile) + 1) * 8;
+  z.ntasks = static_cast<size_t>(L.task_lists) * kTaskStride * 8;
+  z.rows_at = align_up(static_cast<size_t>(L.task_lists) * L.task_cap * sizeof(uint2));
+  z.groups_at = z.rows_at + (chunks << bits) * 4;
+  z.shared = std::max(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
+                          (narrow_words(cap_pairs) ? 4 : 8),
+                      z.groups_at + (groups << bits) * 4);
+  return z;
+}
+
 // Workspace of a build by records.  It takes no more than make_layout's for the
 // same build except for its list of segments, so a build runs by records where
 // that fits what the caller was asked for.
@@ -343,20 +375,13 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.ncount_tiles = static_cast<uint32_t>(ceil_div(ntris, kCountBlock * kCountK));
   L.nsort_tiles_cap = static_cast<uint32_t>(ceil_div(cap_pairs, kSortTileMin));
   L.ntfo = L.nsort_tiles_cap + 1;
-  L.list_cap = static_cast<uint32_t>(std::min<uint64_t>(rp.code.nsegs, cap_pairs));
-  // lists of tasks: a wave adds at most four entries (and the first one more), and
-  // there are no more crowded segments and long stretches than pairs and segments allow
-  const uint32_t bits = rp.code.wx + rp.code.wy, blocks = static_cast<uint32_t>(ceil_div(L.list_cap, kFinishRun));
-  L.task_lists = 1;
-  while (L.task_lists < kTaskLists && L.task_lists * 128 < blocks) L.task_lists *= 2;
-  L.task_cap = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(blocks, L.task_lists) * 4 + 1,
-                                                        cap_pairs / kCrowdLeast + rp.code.nsegs / (kGapWave >> bits) + 2));
+  const RecordSizes z = record_sizes(cap_pairs, rp, L);
   L.ctl = take(sizeof(Control));
   L.hist = take(static_cast<size_t>(kHistCopies) * 4 * kRadixMax * sizeof(uint32_t));
   L.count_status = take(std::max<size_t>(L.ncount_tiles, 1) * 8);
   L.grid_pairs = take(static_cast<size_t>(ngrids) * 8);
-  L.list_status = take((ceil_div(cap_pairs, kSegListTile) + 1) * 8);
-  L.ntasks = take(static_cast<size_t>(L.task_lists) * kTaskStride * 8);
+  L.list_status = take(z.list_status);
+  L.ntasks = take(z.ntasks);
   L.cull_status = take(culled ? static_cast<size_t>(L.ntfo) * 8 : 0);
   L.zero_end = o;
   L.start = take(ntris * 4);
@@ -365,17 +390,10 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.tfg = take(batched ? static_cast<size_t>(L.ntfo) * 4 : 0);
   L.tfo_work = take(tfo_work_cap(L.ntfo) * sizeof(uint4));
   L.cull_rec = take(culled ? ntris * sizeof(CullRecord) : 0);
-  // the tasks and the chunks' counts come after the radix passes, where those keep their
-  // look-back words (rows only where a segment can hold several chunks)
-  const uint64_t chunks = cap_pairs < 2 * kChunkPairs ? 0 : ceil_div(cap_pairs, kChunkPairs);
-  const uint64_t groups = chunks < 2 * kGroupChunks ? 0 : ceil_div(chunks, kGroupChunks);
-  const size_t tasks_size = align_up(static_cast<size_t>(L.task_lists) * L.task_cap * sizeof(uint2));
-  L.sort_status = take(std::max(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
-                                    (narrow_words(cap_pairs) ? 4 : 8),
-                                tasks_size + ((chunks + groups) << bits) * 4));
+  L.sort_status = take(z.shared);
   L.tasks = L.sort_status;
-  L.rows = L.tasks + tasks_size;
-  L.groups = L.rows + (chunks << bits) * 4;
+  L.rows = L.sort_status + z.rows_at;
+  L.groups = L.sort_status + z.groups_at;
   L.keys_alt = take(cap_pairs * 4);
   L.vals_alt = take(cap_pairs * 4);
   L.keys_alt2 = take(batched ? cap_pairs * 4 : 0);
@@ -383,9 +401,41 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.run = take((ngrids + 1) * sizeof(GridRun));
   L.npairs_out = take((ngrids + 1) * 8);
   L.table = take(batched ? ngrids * sizeof(GridDev) : 0);
-  L.list = take((static_cast<size_t>(L.list_cap) + 1) * sizeof(SegEntry));
+  L.list = take(z.list);
   L.total = o + 256;
   return L;
+}
+
+// A batch split around its count is counted both ways, pairs and records, and its
+// second half, which knows the outputs, takes either.  Its records' layout is the
+// pairs' (P) but for what only they need, which lies where the pairs' radix passes
+// would keep their look-back words: those of the records are fewer and half as
+// wide.  False when it does not fit there.
+bool make_split_layout(const Layout& P, uint64_t ntris, uint64_t cap_pairs, const RecordPlan& rp, Layout* out) {
+  Layout L = P;
+  const RecordSizes z = record_sizes(cap_pairs, rp, L);
+  size_t o = P.sort_status;
+  auto take = [&](size_t bytes) {
+    size_t at = o;
+    o = align_up(o + std::max<size_t>(bytes, 1));
+    return at;
+  };
+  L.zero2 = o;
+  L.rec_status = take(std::max<size_t>(L.ncount_tiles, 1) * 8);
+  L.list_status = take(z.list_status);
+  L.ntasks = take(z.ntasks);
+  L.zero2_end = o;
+  L.start = take(ntris * 4);
+  L.tfo = take(static_cast<size_t>(L.ntfo) * 4);
+  L.tfg = take(static_cast<size_t>(L.ntfo) * 4);
+  L.tfo_work = take(tfo_work_cap(L.ntfo) * sizeof(uint4));
+  L.list = take(z.list);
+  L.sort_status = take(z.shared);
+  L.tasks = L.sort_status;
+  L.rows = L.sort_status + z.rows_at;
+  L.groups = L.sort_status + z.groups_at;
+  *out = L;
+  return o <= P.keys_alt;
 }
 
 template <class T>
@@ -424,17 +474,17 @@ GridDev make_grid(const float* verts, uint32_t nverts, const uint32_t* tris, uin
 }
 
 // ---- the launch sequence ------------------------------------------------------------
-__global__ void zero_kernel(uint64_t* p, uint64_t nwords) {
-  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < nwords;
+__global__ void zero_kernel(uint64_t* p, uint64_t nwords, uint64_t* q, uint64_t qwords) {
+  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < nwords + qwords;
        i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    p[i] = 0;
+    (i < nwords ? p : q - nwords)[i] = 0;
 }
 
-int launch_zero(void* ws, size_t bytes, hipStream_t s) {
-  const uint64_t words = bytes / 8;
-  const uint32_t blocks = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(words, 256), 1024));
+int launch_zero(void* ws, size_t bytes, hipStream_t s, size_t from = 0, size_t to = 0) {
+  const uint64_t words = bytes / 8, more = (to - from) / 8;
+  const uint32_t blocks = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(words + more, 256), 1024));
   TraceScope ts(s, "zero");
-  zero_kernel<<<std::max(blocks, 1u), 256, 0, s>>>(static_cast<uint64_t*>(ws), words);
+  zero_kernel<<<std::max(blocks, 1u), 256, 0, s>>>(static_cast<uint64_t*>(ws), words, at<uint64_t>(ws, from), more);
   GB_LAUNCHED();
   return GRID_OK;
 }
@@ -460,6 +510,9 @@ struct Build {
   bool no_alloc = false;  // the build may not allocate, not even host memory for its readback
   int sort_shape = 3;     // tile shape of the radix passes from arrays (build_sort_shape)
   bool rec = false;       // the build sorts records (records.hpp), not pairs
+  bool both = false;      // a batch split around its count: counted both ways, L being the pairs' layout ...
+  RecordPlan rec_plan{};  // ... and these the records'
+  Layout rec_L{};
   SegCode code{};
   uint64_t rec_cap = 0;   // ... and the launches' pair capacity
 };
@@ -500,19 +553,21 @@ bool cull_records_pay(uint64_t box_pairs, uint64_t ntris, int pair_passes, int r
   return 5 * box_pairs >= 12 * ntris && (box_pairs >= kCullRecordsFew || record_passes < pair_passes);
 }
 
+// The launch of a wave per kFinishRun listed segments takes at most 2^32 - 1 threads.
+bool listable(const Layout& L) { return ceil_div(L.list_cap, kFinishRun) * kWave <= 0xFFFFFFFFull; }
+
 // Makes b a build by records when its grids, about `pairs` pairs, allow it and the workspace holds it.
 void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t cap, uint64_t pairs, size_t ws_bytes) {
   if (b.ntris == 0 || cap == 0) return;
   RecordPlan rp{};
   Layout L{};
-  // a workspace too small for the list of segments, or more of them than a launch of
-  // a wave per kFinishRun takes (2^32 - 1 threads): wider segments, fewer of them
+  // a workspace too small for the list of segments: wider segments, fewer of them
   for (uint32_t wider = 0;; ++wider) {
     if (!plan_records(grids, ngrids, cells, pairs, wider, b.culled, &rp)) return;
     const int pp = b.plan.sp.passes, rpp = rp.plan.sp.passes;
     if (!(b.culled ? cull_records_pay(cap, b.ntris, pp, rpp) : records_pay(pairs, b.ntris, pp, rpp))) return;
     L = make_record_layout(b.ntris, cap, rp, ngrids, b.batched, b.culled);
-    if (L.total <= ws_bytes && ceil_div(L.list_cap, kFinishRun) * kWave <= 0xFFFFFFFFull) break;
+    if (L.total <= ws_bytes && listable(L)) break;
   }
   b.rec = true;
   b.code = rp.code;
@@ -520,26 +575,52 @@ void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint
   b.L = L;
 }
 
+// A batch split around its count knows only the triangles when it cuts the grids
+// into segments, and both halves must cut them alike: as for so many pairs each.
+constexpr uint64_t kPairsPerTriangle = 6;
+// Batches of fewer triangles are not worth a count both ways (2 to 3 us): they go
+// by pairs.  Split builds, us, by a guess of six pairs a triangle alone and so:
+// mesh of 2M 286 / 203, of 300k 139 / 121; mixed 200k 115 / 117, 8 x 100k 167 / 169.
+constexpr uint32_t kBothTriangles = 1u << 15;
+
+// Makes b, a batch split around its count, one that is counted both ways, where its
+// second half may go by records.
+void try_both(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t cap) {
+  if (g_fused_expand || b.ntris < kBothTriangles || cap == 0) return;
+  const uint64_t pairs = std::min<uint64_t>(cap, kPairsPerTriangle * b.ntris);
+  for (uint32_t wider = 0; plan_records(grids, ngrids, cells, pairs, wider, false, &b.rec_plan); ++wider) {
+    b.both = make_split_layout(b.L, b.ntris, cap, b.rec_plan, &b.rec_L) && listable(b.rec_L);
+    if (b.both) return;
+  }
+  b.rec_L = Layout{};
+}
+
 template <bool B>
 int launch_count(Build& b) {
   if (b.ntris == 0) return GRID_OK;
+  Control* const ctl = at<Control>(b.ws, b.L.ctl);
+  auto tables = [&](const Layout& L, size_t status, uint32_t* work_n, uint64_t* total) {
+    return CountTables{at<uint32_t>(b.ws, L.start),   at<uint32_t>(b.ws, L.tfo),   at<uint32_t>(b.ws, L.tfg),
+                       at<uint64_t>(b.ws, status),    at<uint4>(b.ws, L.tfo_work), work_n, total};
+  };
   CountArgs a{};
   a.gs = b.gs;
   a.ntris = b.ntris;
-  a.start = at<uint32_t>(b.ws, b.L.start);
   a.box = at<uint64_t>(b.ws, b.L.box);
-  a.tfo = at<uint32_t>(b.ws, b.L.tfo);
-  a.tfg = at<uint32_t>(b.ws, b.L.tfg);
   a.ntfo = b.L.ntfo;
   a.tile_shift = kExpandTileShift;
-  a.status = at<uint64_t>(b.ws, b.L.count_status);
-  a.tfo_work = at<uint4>(b.ws, b.L.tfo_work);
   a.tfo_work_cap = tfo_work_cap(b.L.ntfo);
-  a.ctl = at<Control>(b.ws, b.L.ctl);
+  a.t = tables(b.L, b.L.count_status, &ctl->tfo_work_n, b.rec ? &ctl->nitems : &ctl->npairs);
+  if (b.both) a.rec = tables(b.rec_L, b.rec_L.rec_status, &ctl->rec_work_n, &ctl->nitems);
+  a.ctl = ctl;
   a.grid_pairs = at<uint64_t>(b.ws, b.L.grid_pairs);
   TraceScope ts(b.s, "count_scan");
-  if (b.rec) count_kernel<kCountBlock, kCountK, B, true><<<b.L.ncount_tiles, kCountBlock, 0, b.s>>>(a);
-  else count_kernel<kCountBlock, kCountK, B><<<b.L.ncount_tiles, kCountBlock, 0, b.s>>>(a);
+  const uint32_t n = b.L.ncount_tiles;
+  if constexpr (B) {
+    if (b.both) count_kernel<kCountBlock, kCountK, B, kCountBoth><<<n, kCountBlock, 0, b.s>>>(a);
+  }
+  if (b.rec) count_kernel<kCountBlock, kCountK, B, kCountRecords><<<n, kCountBlock, 0, b.s>>>(a);
+  else if (!b.both) count_kernel<kCountBlock, kCountK, B, kCountPairs><<<n, kCountBlock, 0, b.s>>>(a);
   GB_LAUNCHED();
   return GRID_OK;
 }
@@ -559,6 +640,11 @@ int launch_plan(Build& b) {
   a.tfg = at<uint32_t>(b.ws, b.L.tfg);
   a.tfo_work = at<uint4>(b.ws, b.L.tfo_work);
   a.tfo_work_cap = tfo_work_cap(b.L.ntfo);
+  if (b.both) {
+    a.rec_tfo = at<uint32_t>(b.ws, b.rec_L.tfo);
+    a.rec_tfg = at<uint32_t>(b.ws, b.rec_L.tfg);
+    a.rec_tfo_work = at<uint4>(b.ws, b.rec_L.tfo_work);
+  }
   a.ctl = at<Control>(b.ws, b.L.ctl);
   a.grid_pairs = at<uint64_t>(b.ws, b.L.grid_pairs);
   TraceScope ts(b.s, "plan");
@@ -571,7 +657,7 @@ int launch_plan(Build& b) {
 // The start of a build: its control block cleared, its count and its plan.
 template <bool B>
 int launch_counts(Build& b) {
-  int st = launch_zero(b.ws, b.L.zero_end, b.s);
+  int st = launch_zero(b.ws, b.L.zero_end, b.s, b.rec_L.zero2, b.rec_L.zero2_end);
   if (st) return st;
   if ((st = launch_count<B>(b))) return st;
   return launch_plan<B>(b);
@@ -1085,6 +1171,7 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
     a.o.vec16 = ((reinterpret_cast<uintptr_t>(d.k) | reinterpret_cast<uintptr_t>(d.v)) & 15u) == 0;
     a.o.ctl = ctl;
     a.code = b.code;
+    a.run = b.both ? at<GridRun>(b.ws, b.L.run) : nullptr;
     if (!B && b.culled) {
       int st = launch_cull_rows<RB>(b, a, P % 2 ? b.out_cap : npairs, npairs);
       if (st) return st;
@@ -1168,7 +1255,7 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
     auto kern = bits <= 6 ? (b.code.wy ? finish_kernel<finish_cap(6), 64, B, true> : finish_kernel<finish_cap(6), 64, B, false>)
               : bits <= 7 ? (b.code.wy ? finish_kernel<finish_cap(7), 128, B, true> : finish_kernel<finish_cap(7), 128, B, false>)
                           : (b.code.wy ? finish_kernel<finish_cap(8), 256, B, true> : finish_kernel<finish_cap(8), 256, B, false>);
-    kern<<<static_cast<uint32_t>(ceil_div(b.L.list_cap, kFinishRun)), kWave, 0, b.s>>>(a);
+    kern<<<static_cast<uint32_t>(ceil_div(std::min<uint64_t>(b.L.list_cap, npairs), kFinishRun)), kWave, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
   // tasks there can be at most: chunks of crowded segments, pieces of long stretches
@@ -1593,9 +1680,6 @@ uint32_t batch_chunk(const grid_desc* grids, uint32_t ngrids, uint32_t g0) {
 constexpr int64_t kCapFromDescs = -1;
 constexpr int64_t kCapFromWorkspace = -2;
 
-// Pairs per triangle assumed where a build's pair count is not known yet.
-constexpr uint64_t kPairsPerTriangle = 6;
-
 // Largest pair capacity whose batched layout fits in ws_bytes (-1: not even an empty one).
 int64_t batch_pair_capacity(const BatchSetup& bs, uint32_t ngrids, size_t ws_bytes) {
   const Plan plan = make_plan(std::max(1u, bits_for(bs.cells)));
@@ -1644,12 +1728,8 @@ int prepare_batched(Build& b, BatchSetup& bs, const grid_desc* grids, uint32_t n
   b.batch_cells = bs.cells;
   b.L = make_layout(bs.ntris, cap, bs.cells + ngrids, b.plan, ngrids, true);
   if (ws_bytes < b.L.total) return GRID_E_NOMEM;
-  if (!count_only && !g_fused_expand) {
-    // a build split around its count knows only the triangles when it cuts the
-    // grids into segments, and both halves must cut them alike
-    const uint64_t pairs = layout == kCapFromWorkspace ? std::min<uint64_t>(cap, kPairsPerTriangle * bs.ntris) : cap;
-    try_records(b, bs.table.data(), ngrids, bs.cells, cap, pairs, ws_bytes);
-  }
+  if (layout == kCapFromWorkspace) try_both(b, bs.table.data(), ngrids, bs.cells, cap);
+  else if (!count_only && !g_fused_expand) try_records(b, bs.table.data(), ngrids, bs.cells, cap, cap, ws_bytes);
   b.gs = GridSet{};
   b.gs.table = at<GridDev>(ws, b.L.table);
   b.gs.ngrids = ngrids;
@@ -2100,12 +2180,12 @@ int grid_build_batched_counted(const grid_desc* grids, uint32_t ngrids, void* ws
   // a grid beyond its capacity is caught by the sink kernel, pairs beyond the
   // workspace by the count's plan, and either way no kernel writes anything
   const uint64_t n = std::min<uint64_t>(bs.cap, b.layout_cap);
-  if (b.rec) {
-    // the plan again, now with the outputs' capacities: a grid beyond its own is
-    // flagged by a kernel that ends before the first one that acts on the flag
-    // begins (workgroups of one kernel that raise it and read it race)
-    if ((st = launch_plan<true>(b))) return st;
-    return launch_records<true>(b, nullptr, nullptr, std::max<uint64_t>(n, 1));
+  if (b.both && n > 0 && records_pay(n, b.ntris, b.plan.sp.passes, b.rec_plan.plan.sp.passes)) {
+    b.rec = true;
+    b.code = b.rec_plan.code;
+    b.plan = b.rec_plan.plan;
+    b.L = b.rec_L;
+    return launch_records<true>(b, nullptr, nullptr, n);
   }
   if (n > 0) {
     if (b.plan.sp.passes == 0) return GRID_E_INVAL;

@@ -67,22 +67,35 @@ GB_DEV void clear_status(const StatusClear& c, uint64_t npairs) {
 // ---------------------------------------------------------------------------
 // CountCells + ExclusiveSum (one pass, decoupled look-back).
 // ---------------------------------------------------------------------------
+// What the count adds up and hands to the expansion: the triangles' pairs, or
+// their records.
+struct CountTables {
+  uint32_t* start;          // [ntris] exclusive offsets (global)
+  uint32_t* tfo;            // [ntfo] owner of the first item of each expansion tile
+  uint32_t* tfg;            // [ntfo] batched: grid of that owner
+  uint64_t* status;         // [count tiles] look-back words
+  uint4* tfo_work;          // [tfo_work_cap] (object, grid, first entry, last entry) runs left for the plan kernel
+  uint32_t* tfo_work_n;     // ... how many (control block)
+  uint64_t* total;          // (control block)
+};
+enum CountWhat : int {
+  kCountPairs = 0,
+  kCountRecords = 1,        // (a grid's pairs are only added up)
+  kCountBoth = 2,           // pairs, and records beside them
+};
+
 struct CountArgs {
   GridSet gs;
   uint32_t ntris;           // total triangles (all grids)
-  uint32_t* start;          // [ntris] exclusive pair offsets (global)
   uint64_t* box;            // [ntris] packed cell boxes
-  uint32_t* tfo;            // [ntfo] owner of the first pair of each expansion tile
-  uint32_t* tfg;            // [ntfo] batched: grid of that owner
   uint32_t ntfo;
   uint32_t tile_shift;      // log2 of the expansion tile size (one tfo entry per expansion tile)
-  uint64_t* status;         // [count tiles] look-back words
-  uint4* tfo_work;          // [tfo_work_cap] (object, grid, first entry, last entry) runs left for the plan kernel
   uint32_t tfo_work_cap;
-  uint64_t* grid_pairs;     // record builds: [ngrids] each grid's pair count (zeroed), added up per tile
+  CountTables t;            // pairs, or kCountRecords: records
+  CountTables rec;          // kCountBoth
+  uint64_t* grid_pairs;     // kCountRecords: [ngrids] each grid's pair count (zeroed), added up per tile
   Control* ctl;
 };
-
 
 // Grid of triangle t (largest g with tri_base[g] <= t), found by one whole
 // wave: each level probes 64 evenly spaced grids of the remaining range at
@@ -137,12 +150,15 @@ GB_DEV void add_grid_pairs(uint64_t* grid_pairs, uint64_t* s_pairs, uint32_t g0,
 }
 
 // CountCells for the tile's triangles base + (k0 + k) * Block + tid: writes each box
-// and leaves the counts in s_val (striped order).  Rec: what is counted (and
-// later expanded and sorted) are the triangle's records, one per segment its
+// and leaves the counts in s_val (striped order).  kCountRecords: what is counted
+// (and later expanded and sorted) are the triangle's records, one per segment its
 // box meets; its pairs are only added up, per tile into s_pairs[0] (LDS) or, in
-// tiles that straddle grids, per grid from g0 on.
-template <int Block, int K, int Mode, bool Rec>
-GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, uint32_t* s_val, uint64_t* s_pairs, uint32_t g0 = 0, uint32_t k0 = 0) {
+// tiles that straddle grids, per grid from g0 on.  kCountBoth: the records' counts
+// go into s_rec.
+template <int Block, int K, int Mode, int What>
+GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, uint32_t* s_val, uint32_t* s_rec,
+                        uint64_t* s_pairs, uint32_t g0 = 0, uint32_t k0 = 0) {
+  constexpr bool Rec = What == kCountRecords;
   const uint32_t tid = threadIdx.x;
   uint64_t pairs = 0;
   uint32_t g = g0;  // kCountPerItem: the grid of the tile's first triangle, walked forward per item
@@ -188,12 +204,12 @@ GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, ui
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const uint64_t t = base + static_cast<uint64_t>(k0 + k) * Block + tid;
-    uint32_t cnt = 0;
+    uint32_t cnt = 0, recs = 0;
     uint64_t item_pairs = 0;
     if (t < a.ntris) {
       const GridDev& G = Mode == kCountPerItem ? a.gs.table[gi[k]] : G0;
       uint64_t packed = 0;
-      cnt = 1;
+      cnt = recs = 1;
       if (bad[k]) {
         atomicOr(&a.ctl->error, kErrBadIndex);
       } else {
@@ -209,17 +225,19 @@ GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, ui
         }
         cnt = m[0] * m[1] * m[2];
         packed = pack_box(lo, m);
+        if constexpr (What != kCountPairs)
+          recs = (div_small(lo[0] + m[0] - 1, G.mgx) - div_small(lo[0], G.mgx) + 1) *
+                 (div_small(lo[1] + m[1] - 1, G.mgy) - div_small(lo[1], G.mgy) + 1) * m[2];
         if constexpr (Rec) {
           if constexpr (Mode != kCountPerItem) pairs += cnt;
           else item_pairs = cnt;
-          cnt = (div_small(lo[0] + m[0] - 1, G.mgx) - div_small(lo[0], G.mgx) + 1) *
-                (div_small(lo[1] + m[1] - 1, G.mgy) - div_small(lo[1], G.mgy) + 1) * m[2];
         }
       }
       a.box[t] = packed;
     }
     if constexpr (Rec && Mode == kCountPerItem) add_grid_pairs(a.grid_pairs, s_pairs, g0, gi[k], item_pairs);
-    s_val[pad32((k0 + k) * Block + tid)] = cnt;
+    s_val[pad32((k0 + k) * Block + tid)] = Rec ? recs : cnt;
+    if constexpr (What == kCountBoth) s_rec[pad32((k0 + k) * Block + tid)] = recs;
   }
   if constexpr (Rec && Mode != kCountPerItem) {
     const uint64_t sum = wave_sum34(pairs);
@@ -227,50 +245,16 @@ GB_DEV void count_items(const CountArgs& a, const GridDev& G0, uint64_t base, ui
   }
 }
 
-template <int Block, int K, bool Batched, bool Rec = false>
-__global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
+// A count tile's counts in s_val (striped order) made offsets of all tiles, with
+// the owners of the expansion tiles that begin in them.  gl: the grid of the
+// tile's first triangle; one: that of all of them.
+template <int Block, int K, bool Batched>
+GB_DEV void count_offsets(const CountArgs& a, const CountTables& o, uint32_t tile, uint32_t gl, bool one, uint32_t* s_val,
+                          uint64_t* s_wtot, uint64_t* s_prefix) {
   constexpr int Tile = Block * K;
-  __shared__ uint32_t s_val[padded(Tile)];
-  __shared__ uint64_t s_wtot[Block / kWave];
-  __shared__ uint64_t s_prefix;
-  __shared__ uint64_t s_pairs[Rec ? (Batched ? kTileGrids : 1u) : 1u];
-  __shared__ uint32_t s_tile;
-  if (Rec && threadIdx.x < (Batched ? kTileGrids : 1u)) s_pairs[threadIdx.x] = 0;
-  const uint32_t tile = next_tile(&a.ctl->tile_counter[kCtrCount], &s_tile);
   const uint32_t tid = threadIdx.x;
   const uint64_t base = static_cast<uint64_t>(tile) * Tile;
   const uint32_t ntiles = (a.ntris + Tile - 1) / Tile;
-  // batched: the grid of the tile's first triangle, and whether every
-  // triangle of the tile lies in it (the same for the whole workgroup)
-  uint32_t gl = 0;
-  bool one = true;
-  if constexpr (Batched) {
-    const uint32_t t0 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base < a.ntris ? base : a.ntris - 1));
-    const uint64_t e = base + Tile < a.ntris ? base + Tile : a.ntris;
-    const uint32_t t1 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(e - 1));
-    gl = __builtin_amdgcn_readfirstlane(grid_of_tri_wave(a.gs, t0));
-    one = gl + 1 >= a.gs.ngrids || a.gs.table[gl + 1].tri_base > t1;
-    if (one) {
-      const GridDev G = a.gs.table[gl];
-      count_items<Block, K, kCountOneGrid, Rec>(a, G, base, s_val, s_pairs, gl);
-    } else {
-      // four triangles at a time: each carries its own grid's parameters, and all
-      // eight at once would spill
-#pragma unroll 1
-      for (uint32_t k0 = 0; k0 < static_cast<uint32_t>(K); k0 += 4)
-        count_items<Block, 4, kCountPerItem, Rec>(a, a.gs.table[gl], base, s_val, s_pairs, gl, k0);
-    }
-  } else {
-    count_items<Block, K, kCountPlain, Rec>(a, a.gs.one, base, s_val, s_pairs);
-  }
-  __syncthreads();
-
-  if constexpr (Rec) {
-    if (tid < (one ? 1u : kTileGrids)) {
-      const uint64_t p = s_pairs[tid];
-      if (p) add_u64(a.grid_pairs + gl + tid, p);
-    }
-  }
   uint32_t mine[K];
   uint64_t sum = 0;
 #pragma unroll
@@ -281,34 +265,34 @@ __global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
   uint64_t total;
   uint64_t excl = block_exclusive_sum64<Block>(sum, s_wtot, total);
   if (tid < kWave) {
-    const uint64_t p = lookback_wave(a.status, tile, total);
+    const uint64_t p = lookback_wave(o.status, tile, total);
     if (tid == 0) {
-      s_prefix = p;
-      if (tile == ntiles - 1) (Rec ? a.ctl->nitems : a.ctl->npairs) = p + total;  // (the plan adds up a record build's pairs)
+      *s_prefix = p;
+      if (tile == ntiles - 1) *o.total = p + total;
     }
   }
   __syncthreads();
-  excl += s_prefix;
+  excl += *s_prefix;
 
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const uint64_t t = base + static_cast<uint64_t>(tid) * K + k;
     s_val[pad32(tid * K + k)] = static_cast<uint32_t>(excl);
     if (mine[k] != 0 && t < a.ntris) {
-      // expansion tiles whose first pair this object owns
+      // expansion tiles whose first item this object owns
       const OwnedTiles ot = owned_tiles(excl, mine[k], a.tile_shift, a.ntfo);
       if (ot.any) {
         // about one object per expansion tile; its grid is the tile's first
         // or one a few entries after it
         const uint32_t g = one ? gl : grid_of_tri<Batched>(a.gs, static_cast<uint32_t>(t), gl);
         for (uint64_t j = ot.lo; j <= ot.inl; ++j) {
-          a.tfo[j] = static_cast<uint32_t>(t);
-          if constexpr (Batched) a.tfg[j] = g;
+          o.tfo[j] = static_cast<uint32_t>(t);
+          if constexpr (Batched) o.tfg[j] = g;
         }
         if (ot.inl < ot.hi) {  // a huge object: the rest of its run goes to the plan kernel
-          const uint32_t w = atomicAdd(&a.ctl->tfo_work_n, 1u);
+          const uint32_t w = atomicAdd(o.tfo_work_n, 1u);
           if (w < a.tfo_work_cap)
-            a.tfo_work[w] = make_uint4(static_cast<uint32_t>(t), g, static_cast<uint32_t>(ot.inl + 1),
+            o.tfo_work[w] = make_uint4(static_cast<uint32_t>(t), g, static_cast<uint32_t>(ot.inl + 1),
                                        static_cast<uint32_t>(ot.hi));
           else
             atomicOr(&a.ctl->error, kErrInternal);
@@ -321,7 +305,59 @@ __global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const uint64_t t = base + static_cast<uint64_t>(k) * Block + tid;
-    if (t < a.ntris) a.start[t] = s_val[pad32(k * Block + tid)];
+    if (t < a.ntris) o.start[t] = s_val[pad32(k * Block + tid)];
+  }
+}
+
+template <int Block, int K, bool Batched, int What = kCountPairs>
+__global__ __launch_bounds__(Block) void count_kernel(CountArgs a) {
+  constexpr int Tile = Block * K;
+  constexpr bool Rec = What == kCountRecords;
+  __shared__ uint32_t s_val[padded(Tile)];
+  __shared__ uint32_t s_rec[What == kCountBoth ? padded(Tile) : 1];
+  __shared__ uint64_t s_wtot[Block / kWave];
+  __shared__ uint64_t s_prefix;
+  __shared__ uint64_t s_pairs[Rec ? (Batched ? kTileGrids : 1u) : 1u];
+  __shared__ uint32_t s_tile;
+  if (Rec && threadIdx.x < (Batched ? kTileGrids : 1u)) s_pairs[threadIdx.x] = 0;
+  const uint32_t tile = next_tile(&a.ctl->tile_counter[kCtrCount], &s_tile);
+  const uint32_t tid = threadIdx.x;
+  const uint64_t base = static_cast<uint64_t>(tile) * Tile;
+  // batched: the grid of the tile's first triangle, and whether every
+  // triangle of the tile lies in it (the same for the whole workgroup)
+  uint32_t gl = 0;
+  bool one = true;
+  if constexpr (Batched) {
+    const uint32_t t0 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base < a.ntris ? base : a.ntris - 1));
+    const uint64_t e = base + Tile < a.ntris ? base + Tile : a.ntris;
+    const uint32_t t1 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(e - 1));
+    gl = __builtin_amdgcn_readfirstlane(grid_of_tri_wave(a.gs, t0));
+    one = gl + 1 >= a.gs.ngrids || a.gs.table[gl + 1].tri_base > t1;
+    if (one) {
+      const GridDev G = a.gs.table[gl];
+      count_items<Block, K, kCountOneGrid, What>(a, G, base, s_val, s_rec, s_pairs, gl);
+    } else {
+      // four triangles at a time: each carries its own grid's parameters, and all
+      // eight at once would spill
+#pragma unroll 1
+      for (uint32_t k0 = 0; k0 < static_cast<uint32_t>(K); k0 += 4)
+        count_items<Block, 4, kCountPerItem, What>(a, a.gs.table[gl], base, s_val, s_rec, s_pairs, gl, k0);
+    }
+  } else {
+    count_items<Block, K, kCountPlain, What>(a, a.gs.one, base, s_val, s_rec, s_pairs);
+  }
+  __syncthreads();
+
+  if constexpr (Rec) {  // (the plan adds up a record build's pairs)
+    if (tid < (one ? 1u : kTileGrids)) {
+      const uint64_t p = s_pairs[tid];
+      if (p) add_u64(a.grid_pairs + gl + tid, p);
+    }
+  }
+  count_offsets<Block, K, Batched>(a, a.t, tile, gl, one, s_val, s_wtot, &s_prefix);
+  if constexpr (What == kCountBoth) {
+    __syncthreads();  // (s_prefix)
+    count_offsets<Block, K, Batched>(a, a.rec, tile, gl, one, s_rec, s_wtot, &s_prefix);
   }
 }
 

@@ -36,6 +36,9 @@ struct PlanArgs {
   uint32_t* tfg;
   const uint4* tfo_work;   // ... and the runs of it the count left for this kernel
   uint32_t tfo_work_cap;
+  uint32_t* rec_tfo;       // batches counted both ways: the same of the records (else null)
+  uint32_t* rec_tfg;
+  const uint4* rec_tfo_work;
   const uint64_t* grid_pairs;  // record builds: each grid's pair count (else they come from start)
   Control* ctl;
 };
@@ -43,17 +46,19 @@ struct PlanArgs {
 template <int Block, bool Batched, bool Rec = false>
 __global__ __launch_bounds__(Block) void plan_kernel(PlanArgs a) {
   __shared__ uint32_t s_wtot[Block / kWave];
-  {
-    // the tile-owner runs of huge objects, written by the whole workgroup
-    const uint32_t nw = a.ctl->tfo_work_n < a.tfo_work_cap ? a.ctl->tfo_work_n : a.tfo_work_cap;
+  // the tile-owner runs of huge objects, written by the whole workgroup
+  auto owner_runs = [&](uint32_t n, const uint4* work, uint32_t* tfo, uint32_t* tfg) {
+    const uint32_t nw = n < a.tfo_work_cap ? n : a.tfo_work_cap;
     for (uint32_t w = 0; w < nw; ++w) {
-      const uint4 it = a.tfo_work[w];
+      const uint4 it = work[w];
       for (uint32_t j = it.z + threadIdx.x; j <= it.w; j += Block) {
-        a.tfo[j] = it.x;
-        if constexpr (Batched) a.tfg[j] = it.y;
+        tfo[j] = it.x;
+        if constexpr (Batched) tfg[j] = it.y;
       }
     }
-  }
+  };
+  owner_runs(a.ctl->tfo_work_n, a.tfo_work, a.tfo, a.tfg);
+  if (a.rec_tfo) owner_runs(a.ctl->rec_work_n, a.rec_tfo_work, a.rec_tfo, a.rec_tfg);
   const uint32_t G = a.gs.ngrids;
   uint64_t total;
   if constexpr (Rec) {

@@ -41,7 +41,18 @@ struct SegCode {
 struct RecordArgs {
   ExpandOutArgs o;          // cells/objs receive the records' keys and values
   SegCode code;
+  const GridRun* run;       // batches resumed from their count: each grid's pair count, to check its outputs by (else null)
 };
+
+// A batch resumed from its count learns its outputs only then: whether some grid's
+// are too small.  Every wave looks at all grids, so all of them come to the same
+// answer by themselves: a flag that one workgroup raises while others read it would
+// stop some waves of a workgroup and leave the rest to scan totals never written.
+GB_DEV bool outputs_too_small(const GridSet& s, const GridRun* run) {
+  bool over = false;
+  for (uint32_t g = lane_id(); g < s.ngrids; g += kWave) over = over || run[g].npairs > s.table[g].cap_pairs;
+  return ballot(over) != 0;
+}
 
 // What the expansion needs of an object's grid.
 struct SegParams {
@@ -145,6 +156,12 @@ __global__ __launch_bounds__(Block, 8) void record_kernel(RecordArgs a) {
   __shared__ uint32_t s_hist[4 * R];
   __shared__ uint32_t s_wtot[Block / kWave];
   if (build_failed(a.o.ctl)) return;
+  if constexpr (Batched) {
+    if (a.run && outputs_too_small(a.o.ex.gs, a.run)) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&a.o.ctl->cap_flag, 1u);  // for the kernels that follow
+      return;
+    }
+  }
   const uint64_t nrec = a.o.ctl->nitems;
   const uint32_t ntiles = static_cast<uint32_t>((nrec + N - 1) / N);
   clear_status<Block>(a.o.clear, nrec);

@@ -207,9 +207,9 @@ def test_split_builds_interleaved_on_two_streams(G):
     _oracle_equal(ob, b)
 
 
-def test_split_by_records_checks_capacities_before_its_kernels(G):
-    # a batch that is built by records: the outputs' capacities are checked by a kernel of their own (the plan,
-    # run again once the outputs are known), so no workgroup can meet the flag half raised
+def test_split_by_records_checks_capacities(G):
+    # a batch that is built by records, whose first kernel is where its outputs' capacities are known: every wave
+    # checks them by itself, and nothing is written when one is too small
     batch = _batch(48, [60_000, 50_000, 70_000])
     inputs = [G.GridInput.from_scene(s) for s in batch]
     caps = G.count_batched(inputs)
@@ -230,9 +230,63 @@ def test_split_by_records_checks_capacities_before_its_kernels(G):
         finally:
             k = G.trace_read()
             G.trace_enable(False)
-        assert "records" in k and "plan" in k, sorted(k)
+        assert "records" in k, sorted(k)
         assert G.workspace_status(ws)[0] == (G.GRID_E_CAPACITY if less else G.GRID_OK)
         if less:
             assert _untouched(outs)
         else:
             _oracle_equal(outs, batch)
+
+
+def _resumed(G, batch):
+    """The kernels of the second half, after the results are checked."""
+    inputs = [G.GridInput.from_scene(s) for s in batch]
+    caps = G.count_batched(inputs)
+    ws = G.Workspace()
+    wsb = _ws_bytes(G, inputs, caps)
+    ws.get(wsb)
+    h = _Half(G, len(batch))
+    _, counts, status = _count(G, inputs, ws, wsb, h)
+    assert counts == caps and status == 0
+    outs = _filled(G, inputs, caps)
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        G.build_batched_counted(inputs, outs, caps, ws, wsb, h.stage)
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+    assert G.workspace_status(ws)[0] == G.GRID_OK
+    _oracle_equal(outs, batch)
+    return k
+
+
+def test_split_builds_go_by_what_was_counted(G):
+    # the second half knows the pairs: few a triangle are sorted as pairs whatever the triangles alone suggest
+    rng = np.random.default_rng(49)
+    few = []
+    for n in (150_000, 90_001):
+        c = rng.uniform(0.0, 10.0, (n, 1, 3))
+        verts, tris = scenes.soup_from_vertices(c + rng.uniform(-0.01, 0.01, (n, 3, 3)))
+        lo, hi = scenes.aabb_bounds(verts)
+        few.append(scenes.Scene(f"few{n}", verts, tris, lo, hi, scenes.resolution_rule(lo, hi, n, 4.0, 512)))
+    _say("split, few pairs a triangle")
+    k = _resumed(G, few)
+    assert "finish" not in k and "onesweep_grids" in k, sorted(k)
+    _say("split, many pairs a triangle")
+    k = _resumed(G, [few[0]] + _batch(50, [120_000, 0, 150_000]))
+    assert "finish" in k and "onesweep_grids" not in k, sorted(k)
+
+
+def test_split_by_records_of_huge_triangles(G):
+    # triangles of thousands of records among small ones: the runs of tile owners that the count leaves to the plan
+    batch = _batch(51, [40_000, 30_000])
+    big = np.asarray([[[0.01, 0.01, 0.01], [9.99, 0.02, 9.98], [5.0, 9.99, 5.0]], [[9.8, 9.7, 2.0], [0.3, 5.0, 9.0], [6.0, 0.2, 4.0]]])
+    for s, at in zip(batch, (0, 20_000)):
+        for i, b in enumerate(big):
+            t = s.tris[at + 9 * i]
+            s.verts[:, t] = b.T
+        s.res = np.asarray([300, 300, 300], np.uint32)
+    _say("split, huge triangles")
+    k = _resumed(G, batch)
+    assert "finish" in k, sorted(k)
