@@ -73,7 +73,11 @@ typedef struct grid_out {
   uint32_t *objs;      /* [cap_pairs] object ids, ascending within each cell    */
   uint32_t *ranges;    /* [2 * R] (begin, end) per cell, x-fastest cell order   */
   uint64_t cap_pairs;  /* in: capacity of cells/objs, in pairs                  */
-  uint64_t npairs;     /* out: NO, the number of <obj, cell> pairs              */
+  uint64_t npairs;     /* out: NO, the number of <obj, cell> pairs.  In: the pairs to
+                          expect where cap_pairs leaves room (a count, the last
+                          frame's), 0 if unknown: plain and batched builds choose
+                          their kernels by it (by cap_pairs when it is 0 or above
+                          cap_pairs); no result or limit depends on it            */
 } grid_out;
 
 /* One grid of a batch: the same arguments as grid_build, plus its outputs. */

@@ -268,7 +268,8 @@ def count(g: GridInput, ws: Optional[Workspace] = None, with_start: bool = False
 
 def build(g: GridInput, cap_pairs: Optional[int] = None, ws: Optional[Workspace] = None, out: Optional[GridResult] = None,
           stream=None) -> GridResult:
-    """The whole build.  With no capacity given, counts first to size the outputs."""
+    """The whole build.  With no capacity given, counts first to size the outputs.  An output that was built
+    into before says by its npairs how many pairs to expect (here and in the other builds into given outputs)."""
     L = lib()
     ws = ws or default_workspace(g.verts.device)
     if out is None:
@@ -280,7 +281,7 @@ def build(g: GridInput, cap_pairs: Optional[int] = None, ws: Optional[Workspace]
                          torch.empty(2 * g.ncells, dtype=torch.int32, device=dev), 0)
     cap = int(out.cells.numel()) if cap_pairs is None else int(cap_pairs)
     wp, wn = ws.ptr_size(workspace_size(g.ntris, cap, g.res))
-    o = grid_out(out.cells.data_ptr(), out.objs.data_ptr(), out.ranges.data_ptr(), cap, 0)
+    o = grid_out(out.cells.data_ptr(), out.objs.data_ptr(), out.ranges.data_ptr(), cap, int(out.npairs))
     st = L.grid_build(*_input_args(g), wp, wn, C.byref(o), _stream(stream))
     out.npairs = int(o.npairs)
     _check(st, "grid_build")
@@ -291,7 +292,7 @@ def build_static(g: GridInput, out: GridResult, stream=None) -> GridResult:
     """The whole build in the library's static device scratch (grid_build_static):
     no workspace argument and no allocation.  out's buffers set the capacity."""
     cap = int(out.cells.numel())
-    o = grid_out(out.cells.data_ptr(), out.objs.data_ptr(), out.ranges.data_ptr(), cap, 0)
+    o = grid_out(out.cells.data_ptr(), out.objs.data_ptr(), out.ranges.data_ptr(), cap, int(out.npairs))
     st = lib().grid_build_static(*_input_args(g), C.byref(o), _stream(stream))
     out.npairs = int(o.npairs)
     _check(st, "grid_build_static")
@@ -333,7 +334,7 @@ class PlainBuild:
         self.ws = ws or default_workspace(g.verts.device)
         cap = int(out.cells.numel())
         wp, wn = self.ws.ptr_size(workspace_size(g.ntris, cap, g.res))
-        self._o = grid_out(out.cells.data_ptr(), out.objs.data_ptr(), out.ranges.data_ptr(), cap, 0)
+        self._o = grid_out(out.cells.data_ptr(), out.objs.data_ptr(), out.ranges.data_ptr(), cap, int(out.npairs))
         self._fn = lib().grid_build
         self._args = (*_input_args(g), wp, wn, C.byref(self._o), _stream(stream))
 
@@ -424,32 +425,38 @@ def _desc_bytes(g: GridInput) -> bytes:
     return b
 
 
-def _set_outputs(arr, cells: List[int], objs: List[int], ranges: List[int], caps: List[int]):
-    """Write output addresses and pair capacities into a descriptor array."""
+def _set_outputs(arr, cells: List[int], objs: List[int], ranges: List[int], caps: List[int],
+                 npairs: Optional[List[int]] = None):
+    """Write output addresses and pair capacities (and the pairs to expect) into a descriptor array."""
     if len(arr) <= _FEW:
-        for d, c, o, r, k in zip(arr, cells, objs, ranges, caps):
+        for d, c, o, r, k, p in zip(arr, cells, objs, ranges, caps, npairs or [0] * len(arr)):
             out = d.out
             out.cells = c
             out.objs = o
             out.ranges = r
             out.cap_pairs = k
+            out.npairs = p
         return
     a = _desc_view(arr)
+    if npairs:
+        a["npairs"] = npairs
     a["cells"] = cells
     a["objs"] = objs
     a["ranges"] = ranges
     a["cap_pairs"] = caps
 
 
-def _descs(inputs: List[GridInput], outs: Optional[List[GridResult]] = None):
+def _descs(inputs: List[GridInput], outs: Optional[List[GridResult]] = None, npairs: Optional[List[int]] = None):
     """ctypes array of grid_desc for the inputs (and outputs): short arrays from each grid's kept
-    descriptor, long ones column by column."""
+    descriptor, long ones column by column.  npairs: the pairs to expect (else the outputs' own)."""
     n = len(inputs)
+    if outs is not None:
+        npairs = [int(x) for x in npairs] if npairs is not None else [int(o.npairs) for o in outs]
     if 0 < n <= _FEW:
         arr = (grid_desc * n).from_buffer_copy(b"".join(_desc_bytes(g) for g in inputs))
         if outs is not None:
             _set_outputs(arr, [o.cells.data_ptr() for o in outs], [o.objs.data_ptr() for o in outs],
-                         [o.ranges.data_ptr() for o in outs], [o.cells.numel() for o in outs])
+                         [o.ranges.data_ptr() for o in outs], [o.cells.numel() for o in outs], npairs)
         return arr
     arr = (grid_desc * n)()
     if n == 0:
@@ -467,6 +474,7 @@ def _descs(inputs: List[GridInput], outs: Optional[List[GridResult]] = None):
         a["objs"] = [o.objs.data_ptr() for o in outs]
         a["ranges"] = [o.ranges.data_ptr() for o in outs]
         a["cap_pairs"] = [o.cells.numel() for o in outs]
+        a["npairs"] = npairs
     return arr
 
 
@@ -613,7 +621,7 @@ def build_batched_async(inputs: List[GridInput], outs: List[GridResult], npairs:
     bytes that must stay untouched until the stream passes this call.  Errors found on the device
     are read later with workspace_status(ws)."""
     L = lib()
-    arr = _descs(inputs, outs)
+    arr = _descs(inputs, outs, npairs)
     n = len(inputs)
     need = int(L.grid_batch_staging_size(n))
     assert staging.is_pinned() and staging.numel() >= need
@@ -662,7 +670,7 @@ def build_batched_counted(inputs: List[GridInput], outs: Optional[List[GridResul
     descriptor array with the outputs already written (then ``outs`` may be None)."""
     L = lib()
     n = len(inputs)
-    st = L.grid_build_batched_counted(descs if descs is not None else _descs(inputs, outs), n, C.c_void_p(ws.buf.data_ptr()), C.c_size_t(ws_bytes),
+    st = L.grid_build_batched_counted(descs if descs is not None else _descs(inputs, outs, npairs), n, C.c_void_p(ws.buf.data_ptr()), C.c_size_t(ws_bytes),
                                       C.c_void_p(staging.data_ptr()), C.c_size_t(staging.numel()), _stream(stream))
     _check(st, "grid_build_batched_counted")
     for o, c in zip(outs or [], npairs):

@@ -515,6 +515,7 @@ struct Build {
   Layout rec_L{};
   SegCode code{};
   uint64_t rec_cap = 0;   // ... and the launches' pair capacity
+  uint64_t expect = 0;    // ... of which about so many are expected
 };
 
 // Whether a plain sorted build under the current knobs may run by records: the
@@ -556,6 +557,13 @@ bool cull_records_pay(uint64_t box_pairs, uint64_t ntris, int pair_passes, int r
 // The launch of a wave per kFinishRun listed segments takes at most 2^32 - 1 threads.
 bool listable(const Layout& L) { return ceil_div(L.list_cap, kFinishRun) * kWave <= 0xFFFFFFFFull; }
 
+// Pairs to expect of a grid's outputs: what the caller says, if it is possible (a
+// count, the last frame's), else the capacity.  It chooses a build's kernels, never
+// its result.  A mesh of 2M triangles, 4.3M pairs, into outputs of twice as many:
+// 226 us by the capacity, by records, and 191 by its pairs; arch-like 10M into three
+// times as many 1001 and 824 (narrower segments than its pairs need).
+uint64_t expected_pairs(const grid_out& o) { return o.npairs > 0 && o.npairs <= o.cap_pairs ? o.npairs : o.cap_pairs; }
+
 // Makes b a build by records when its grids, about `pairs` pairs, allow it and the workspace holds it.
 void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t cap, uint64_t pairs, size_t ws_bytes) {
   if (b.ntris == 0 || cap == 0) return;
@@ -570,6 +578,7 @@ void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint
     if (L.total <= ws_bytes && listable(L)) break;
   }
   b.rec = true;
+  b.expect = pairs;
   b.code = rp.code;
   b.plan = rp.plan;
   b.L = L;
@@ -1152,7 +1161,7 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
   // records of about so many: rows of boxes as wide as high, and no more than half the pairs
-  const double np = static_cast<double>(b.culled ? std::min(npairs, b.out_cap) : npairs), rows = std::cbrt(np / b.ntris);
+  const double np = static_cast<double>(b.culled ? std::min(npairs, b.out_cap) : std::min(npairs, b.expect)), rows = std::cbrt(np / b.ntris);
   b.sort_shape = build_sort_shape(static_cast<uint64_t>(std::min(np / 2, rows * rows * b.ntris)), true);
   b.rec_cap = npairs;
   const Dest bufs[2] = {{at<uint32_t>(b.ws, b.L.keys_alt), at<uint32_t>(b.ws, b.L.vals_alt)},
@@ -1459,7 +1468,7 @@ int build_plain(const float* verts_soa, uint32_t nverts, const uint32_t* tris, u
   const Layout pair_layout = b.L;
   // (path 2 mostly takes the compact path up to kCompactMaxPairs, which needs the pairs' count)
   if ((path == 0 || (path == 2 && out->cap_pairs > kCompactMaxPairs)) && records_allowed())
-    try_records(b, &b.gs.one, 1, ncells_of(res), out->cap_pairs, out->cap_pairs, ws_bytes);
+    try_records(b, &b.gs.one, 1, ncells_of(res), out->cap_pairs, expected_pairs(*out), ws_bytes);
   b.gs.one.out_cells = out->cells;
   b.gs.one.out_objs = out->objs;
   b.gs.one.out_ranges = out->ranges;
@@ -1629,6 +1638,7 @@ namespace {
 struct BatchSetup {
   std::vector<GridDev> table;
   uint64_t ntris = 0, cap = 0, cells = 0;  // cells: the batch's cell space (sum of the grids' cells)
+  uint64_t expect = 0;                     // pairs expected, at most cap
 };
 
 // Sort keys of a batch number the cells of all its grids in one space (each
@@ -1655,6 +1665,7 @@ int setup_batch(const grid_desc* grids, uint32_t ngrids, BatchSetup* bs, bool ne
     bs->table[g] = gd;
     bs->ntris += d.ntris;
     bs->cap += d.out.cap_pairs;
+    bs->expect += expected_pairs(d.out);
     bs->cells += ncells_of(d.res);
   }
   if (bs->ntris >= (1u << 31)) return GRID_E_INVAL;
@@ -1729,7 +1740,7 @@ int prepare_batched(Build& b, BatchSetup& bs, const grid_desc* grids, uint32_t n
   b.L = make_layout(bs.ntris, cap, bs.cells + ngrids, b.plan, ngrids, true);
   if (ws_bytes < b.L.total) return GRID_E_NOMEM;
   if (layout == kCapFromWorkspace) try_both(b, bs.table.data(), ngrids, bs.cells, cap);
-  else if (!count_only && !g_fused_expand) try_records(b, bs.table.data(), ngrids, bs.cells, cap, cap, ws_bytes);
+  else if (!count_only && !g_fused_expand) try_records(b, bs.table.data(), ngrids, bs.cells, cap, bs.expect, ws_bytes);
   b.gs = GridSet{};
   b.gs.table = at<GridDev>(ws, b.L.table);
   b.gs.ngrids = ngrids;
@@ -2180,7 +2191,8 @@ int grid_build_batched_counted(const grid_desc* grids, uint32_t ngrids, void* ws
   // a grid beyond its capacity is caught by the sink kernel, pairs beyond the
   // workspace by the count's plan, and either way no kernel writes anything
   const uint64_t n = std::min<uint64_t>(bs.cap, b.layout_cap);
-  if (b.both && n > 0 && records_pay(n, b.ntris, b.plan.sp.passes, b.rec_plan.plan.sp.passes)) {
+  b.expect = std::min<uint64_t>(n, bs.expect);
+  if (b.both && n > 0 && records_pay(b.expect, b.ntris, b.plan.sp.passes, b.rec_plan.plan.sp.passes)) {
     b.rec = true;
     b.code = b.rec_plan.code;
     b.plan = b.rec_plan.plan;

@@ -176,3 +176,67 @@ def test_statistics_choose_among_all_paths(G, n, over, route):
     assert last == (1 if route == "compact" else 0)
     assert ("finish" in k) == (route == "records") and ("compact_scan" in k) == (route == "compact"), sorted(k)
     _same(r, s)
+
+
+def _kernels(G, f):
+    G.trace_enable(True)
+    G.trace_read()
+    try:
+        r = f()
+        torch.cuda.synchronize()
+    finally:
+        k = G.trace_read()
+        G.trace_enable(False)
+    return r, k
+
+
+def test_outputs_with_room_go_by_the_pairs_expected(G):
+    # one pair a triangle into outputs of six times as many: by the capacity (records) while nothing better is
+    # known, by pairs once the output, or the caller, says how many there are; too many is no answer
+    rng = np.random.default_rng(12)
+    res = (120, 60, 30)
+    lo, _ = _random(rng, 200_000, res, (1, 1, 1))
+    s = _boxes(lo, lo, res, "points with room")
+    g = G.GridInput.from_scene(s)
+    n, _ = G.count(g)
+    out = G.alloc_results([g], [6 * n])[0]
+    b = G.PlainBuild(g, out, G.Workspace())
+    r, k = _kernels(G, b)
+    assert "finish" in k
+    _same(r, s)
+    r, k = _kernels(G, b)
+    assert "finish" not in k
+    _same(r, s)
+    r, k = _kernels(G, lambda: G.build(g, out=out))
+    assert "finish" not in k
+    _same(r, s)
+    out.npairs = 6 * n + 1
+    r, k = _kernels(G, lambda: G.build(g, out=out))
+    assert "finish" in k
+    _same(r, s)
+    # batches: the same, and the asynchronous build is told
+    outs = G.alloc_results([g, g], [6 * n, 6 * n])
+    bb = G.BatchedBuild([g, g], outs, G.Workspace())
+    for first in (True, False):
+        rs, k = _kernels(G, bb)
+        assert ("finish" in k) == first
+        for r in rs:
+            _same(r, s)
+    outs = G.alloc_results([g, g], [6 * n, 6 * n])
+    stage = torch.empty(int(G.lib().grid_batch_staging_size(2)), dtype=torch.uint8, pin_memory=True)
+    ws = G.Workspace()
+    _, k = _kernels(G, lambda: G.build_batched_async([g, g], outs, [n, n], ws, stage))
+    assert "finish" not in k and G.workspace_status(ws) == (G.GRID_OK, 2 * n)
+    for r in outs:
+        _same(r, s)
+
+
+def test_more_pairs_than_expected(G):
+    # an expectation far below the count leaves the result as it is
+    s = scenes.make_scene("mixed", seed=8, ntris=150_000)
+    g = G.GridInput.from_scene(s)
+    n, _ = G.count(g)
+    for say in (1, n // 50, n // 2):
+        out = G.alloc_results([g], [n + 7])[0]
+        out.npairs = say
+        _same(G.PlainBuild(g, out, G.Workspace())(), s)
