@@ -41,6 +41,11 @@ constexpr int kSegListTile = kSegListBlock * kSegListK;
 // tables leave room for it).
 constexpr uint32_t kFinishCap = 1000, kFinishCapDense = 2000;
 constexpr uint32_t finish_cap(uint32_t bits) { return bits <= 6 ? kFinishCapDense : kFinishCap; }
+// Builds of at most this many pairs run no kernel that counts chunks: a launch less
+// (4096 small triangles, 17K pairs: 73 us against 75), and a chunk's workgroup counts
+// its whole segment, should there be one of several chunks (11K of them in a few
+// segments 88 against 93; at 64K records that count alone would take 75).
+constexpr uint64_t kOwnCountPairs = uint64_t{1} << 15;
 constexpr int kScanBlock = 256, kScanK = 8;
 constexpr int kMakePairsBlock = 256;                    // per-object pair generation: one thread per object
 constexpr int kPlanBlock = 1024;
@@ -346,7 +351,7 @@ RecordSizes record_sizes(uint64_t cap_pairs, const RecordPlan& rp, Layout& L) {
   while (L.task_lists < kTaskLists && L.task_lists * 128 < blocks) L.task_lists *= 2;
   L.task_cap = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(blocks, L.task_lists) * 4 + 1,
                                                         cap_pairs / kCrowdLeast + rp.code.nsegs / (kGapWave >> bits) + 2));
-  const uint64_t chunks = cap_pairs < 2 * kChunkPairs ? 0 : ceil_div(cap_pairs, kChunkPairs);
+  const uint64_t chunks = cap_pairs <= kOwnCountPairs ? 0 : ceil_div(cap_pairs, kChunkPairs);
   const uint64_t groups = chunks < 2 * kGroupChunks ? 0 : ceil_div(chunks, kGroupChunks);
   RecordSizes z{};
   z.list = (static_cast<size_t>(L.list_cap) + 1) * sizeof(SegEntry);
@@ -587,10 +592,10 @@ void try_records(Build& b, GridDev* grids, uint32_t ngrids, uint64_t cells, uint
 // A batch split around its count knows only the triangles when it cuts the grids
 // into segments, and both halves must cut them alike: as for so many pairs each.
 constexpr uint64_t kPairsPerTriangle = 6;
-// Batches of fewer triangles are not worth a count both ways (2 to 3 us): they go
+// Batches of fewer triangles are not worth a count both ways (2 to 7 us): they go
 // by pairs.  Split builds, us, by a guess of six pairs a triangle alone and so:
 // mesh of 2M 286 / 203, of 300k 139 / 121; mixed 200k 115 / 117, 8 x 100k 167 / 169.
-constexpr uint32_t kBothTriangles = 1u << 15;
+constexpr uint32_t kBothTriangles = 1u << 16;
 
 // Makes b, a batch split around its count, one that is counted both ways, where its
 // second half may go by records.
@@ -1267,9 +1272,10 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
     kern<<<static_cast<uint32_t>(ceil_div(std::min<uint64_t>(b.L.list_cap, npairs), kFinishRun)), kWave, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
+  if (npairs <= kOwnCountPairs) a.rows = nullptr;
   // tasks there can be at most: chunks of crowded segments, pieces of long stretches
   const uint64_t most = npairs / kCrowdLeast + npairs / kChunkPairs + b.code.nsegs / (kGapWave >> bits) + 1;
-  if (npairs >= 2 * kChunkPairs) {  // (no segment of fewer pairs has several chunks)
+  if (a.rows) {
     TraceScope ts(b.s, "finish_count");
     auto kern = b.code.wy ? finish_count_kernel<B, true> : finish_count_kernel<B, false>;
     kern<<<resident_blocks(kern, kTaskBlock, npairs / kChunkPairs), kTaskBlock, 0, b.s>>>(a);

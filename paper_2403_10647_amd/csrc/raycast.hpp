@@ -202,12 +202,12 @@ __global__ __launch_bounds__(kWave, 4) void raycast_kernel(RaycastArgs a) {
       if (have) {
         if (j2 > hi2 && (up ? k < kend : k > kend)) {
           k += up ? 1 : -1;
-          const float pa = axis_of(G.lo, m) + static_cast<float>(k) * w;
-          float ta, tb;
-          slab_faces(pa, w, om, dm, ta, tb);
+          // faces are numbered as the slabs below them: the far face of one slab is the near one of the next
+          const float lom = axis_of(G.lo, m);
+          const float near = te > -__builtin_inff() ? te : plane_t(lom + static_cast<float>(up ? k : k + 1) * w, om, dm);
           tdone = te;
-          te = fmaxf(ta, tb);
-          const float ps = fmaxf(t0, fminf(ta, tb) - kWalkPad * wt);
+          te = plane_t(lom + static_cast<float>(up ? k + 1 : k) * w, om, dm);
+          const float ps = fmaxf(t0, near - kWalkPad * wt);
           const float pe = fminf(t1, te + kWalkPad * wt);
           if (ps <= pe) {
             {

@@ -407,7 +407,7 @@ struct FinishArgs {
   uint32_t task_cap;        // ... of so many entries each
   uint2* tasks;             // [task_lists][task_cap] (list entry | kTaskGap, its first task in this list)
   uint64_t* ntasks;         // [task_lists * kTaskStride] (zeroed) entries << 32 | tasks
-  uint32_t* rows;           // [ceil(pairs / kChunkPairs)][row_cells] a chunk's pairs per cell
+  uint32_t* rows;           // [ceil(pairs / kChunkPairs)][row_cells] a chunk's pairs per cell (null: not counted beforehand)
   uint32_t* groups;         // [ceil(pairs / (kChunkPairs * kGroupChunks))][row_cells] the same of whole groups
   Control* ctl;
 };
@@ -901,30 +901,55 @@ constexpr uint32_t kTaskDiff = kSegCells + 4;   // a wave's coverage differences
 constexpr uint32_t kTaskCap = 2 * kChunkPairs;  // pairs a workgroup stages
 static_assert(kTaskBlock == kSegCells, "a thread per cell");
 
-// Records [r0, r1) of a chunk, one run per wave (of whole sixteens), counted into
-// the wave's coverage: diff[c] = the run's pairs in cell c.  The caller's barrier
-// follows before other waves' counts are read.
-template <bool Rows>
-GB_DEV RecordRun count_chunk(const FinishArgs& a, uint32_t r0, uint32_t r1, uint32_t width, uint32_t w, uint32_t* diff) {
-  const uint32_t lane = lane_id();
+// A wave's run of records [r0, r1) (whole sixteens) of which there is one a wave.
+GB_DEV RecordRun wave_run(const FinishArgs& a, uint32_t r0, uint32_t r1, uint32_t w) {
   const uint64_t nr = r1 - r0;
   const uint64_t per = (nr + kTaskWaves * 16 - 1) / (kTaskWaves * 16) * 16;
   const uint32_t off0 = static_cast<uint32_t>(w * per < nr ? w * per : nr);
   const uint32_t off1 = static_cast<uint32_t>(off0 + per < nr ? off0 + per : nr);
-  for (uint32_t c = lane; c < kTaskDiff; c += kWave) diff[c] = 0;
+  return RecordRun(a, r0 + off0, r0 + off1);
+}
+GB_DEV void clear_diff(uint32_t* diff) {
+  for (uint32_t c = lane_id(); c < kTaskDiff; c += kWave) diff[c] = 0;
   wave_sync();
-  const RecordRun run(a, r0 + off0, r0 + off1);
-  count_records<Rows>(a, run, width, diff);
+}
+// A wave's coverage differences made counts: diff[c] = its pairs in cell c.
+GB_DEV void sum_diff(uint32_t* diff) {
   wave_sync();
-  // coverage, four consecutive cells per lane
-  uint32_t* cur = diff + 4 * lane;
+  uint32_t* cur = diff + 4 * lane_id();  // four consecutive cells per lane
   const uint32_t x0 = cur[0], x1 = x0 + cur[1], x2 = x1 + cur[2], x3 = x2 + cur[3];
   const uint32_t ci = wave_inclusive(x3, OpAdd{}) - x3;
   cur[0] = ci + x0;
   cur[1] = ci + x1;
   cur[2] = ci + x2;
   cur[3] = ci + x3;
+}
+
+// Records [r0, r1) of a chunk, one run per wave, counted into the wave's diff.
+// The caller's barrier follows before other waves' counts are read.
+template <bool Rows>
+GB_DEV RecordRun count_chunk(const FinishArgs& a, uint32_t r0, uint32_t r1, uint32_t width, uint32_t w, uint32_t* diff) {
+  clear_diff(diff);
+  const RecordRun run = wave_run(a, r0, r1, w);
+  count_records<Rows>(a, run, width, diff);
+  sum_diff(diff);
   return run;
+}
+
+// Any number of records, by the workgroup: pairs of this thread's cell.
+template <bool Rows>
+GB_DEV uint32_t count_cell(const FinishArgs& a, uint32_t r0, uint32_t r1, uint32_t width, uint32_t w, uint32_t* diffs) {
+  constexpr uint32_t kStep = kTaskWaves * RecordRun::kHeld * kWave;  // loaded at once
+  uint32_t* const diff = diffs + w * kTaskDiff;
+  clear_diff(diff);
+  for (uint32_t r = r0; r < r1; r += kStep) count_records<Rows>(a, wave_run(a, r, r1 - r < kStep ? r1 : r + kStep, w), width, diff);
+  sum_diff(diff);
+  __syncthreads();
+  uint32_t n = 0;
+#pragma unroll
+  for (int v = 0; v < kTaskWaves; ++v) n += diffs[v * kTaskDiff + threadIdx.x];
+  __syncthreads();
+  return n;
 }
 
 // First record of chunk c of a segment's `chunks`, of records [r0, r1).
@@ -1017,7 +1042,11 @@ __global__ __launch_bounds__(kTaskBlock) void finish_tasks_kernel(FinishArgs a) 
       const uint32_t cells = row_cells(a.code), groups = groups_of(chunks);
       const uint32_t mine = groups == 0 ? 0u : part / kGroupChunks < groups ? part / kGroupChunks : groups - 1;
       uint32_t before = 0, total = 0, own = 0;
-      if (tid < cells) {
+      if (!a.rows) {  // a small build: no kernel has counted the chunks
+        before = count_cell<Rows>(a, e0.rec, r0, pl.width, w, s_obj);
+        own = count_cell<Rows>(a, r0, r1, pl.width, w, s_obj);
+        total = before + own + count_cell<Rows>(a, r1, e1.rec, pl.width, w, s_obj);
+      } else if (tid < cells) {
         const uint32_t* row = a.rows + static_cast<uint64_t>(row_of(p0)) * cells + tid;
         own = row[static_cast<uint64_t>(part) * cells];
         if (groups) {
