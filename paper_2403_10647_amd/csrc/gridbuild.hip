@@ -742,12 +742,12 @@ int pass_shape(uint64_t n, bool estimate) {
   return !estimate && tiles > cus && 2 * tiles <= 3 * cus ? 0 : 3;
 }
 
-// The sort_shape knob's, where pass_shape would take its default.  Batches of at
-// most eight such tiles of pairs, whose last pass looks each pair's grid up, keep
-// 256 x 16 (one grid of 62K pairs: 118 and 121 us).
-int build_sort_shape(uint64_t n, bool estimate, bool batched = false) {
+// The sort_shape knob's, where pass_shape would take its default.  (Batches, whose
+// last pass looks each pair's grid up, are no exception.  256 x 16 / 1024 x 8, us:
+// one grid of 33K pairs 118.6 120.3, 90K 124 122, 202K 134 126; 4 grids of 24K 133.9
+// 134.7, 54K 140 138, 112K 147 140; 8 of 94K 148 141; 32 of 73K 146 140.)
+int build_sort_shape(uint64_t n, bool estimate) {
   const int shape = g_small_tiles ? pass_shape(n, estimate) : 3;
-  if (shape == 2 && batched && !estimate && n <= 8 * 16384) return 1;
   return shape == 3 ? g_sort_shape : shape;
 }
 
@@ -1043,7 +1043,7 @@ int launch_sort_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t n
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
   const bool fused = fused_first_pass(b);
-  b.sort_shape = build_sort_shape(npairs, false, B);  // before anything sizes or clears the passes' look-back words
+  b.sort_shape = build_sort_shape(npairs, false);  // before anything sizes or clears the passes' look-back words
   const uint32_t* in_k = nullptr;
   const uint32_t* in_v = nullptr;
   if (fused) {
