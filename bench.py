@@ -67,11 +67,24 @@ def dominant(kernels: dict, T: int, NO: int, R: int):
 
 
 def survey_bytes(T: int, NO: int, R: int, passes: int) -> int:
-    """The unfused per-build byte model, at the radix passes the build runs:
+    """The unfused byte model of a build that sorts its pairs in `passes` radix passes:
     80 T + (16 + 16 P) NO + 8 R (inputs, count/start and box round trips, the
     expansion's pairs, one histogram read, P passes that read and write key and
     value, the range pass's read of the sorted cells, and the range table)."""
     return 80 * T + (16 + 16 * passes) * NO + 8 * R
+
+
+def survey_fields(model_bytes: int, pair_passes: int, kernels: dict, builds: int, ms: float) -> dict:
+    """The radix passes a build ran, from its traced launches (name -> (launches, ms) over `builds`
+    builds), and the byte model of sorting its pairs (in pair_passes passes) over its time.  A build
+    by records moves no such bytes: for it the model gives the rate at which a build that sorts
+    pairs would have to move them to be as fast, and no fraction of a roofline."""
+    passes = sum(v[0] for k, v in kernels.items() if k.startswith("onesweep")) / builds
+    frac = round(model_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
+    records = "finish" in kernels
+    return {"radix_passes": int(passes) if passes == int(passes) else passes, "by_records": records,
+            "bytes_survey_model": int(model_bytes), "survey_model_passes": pair_passes,
+            "frac_survey_model": None if records else frac, "pair_sort_equivalent": frac}
 
 
 def source_hash() -> str:
@@ -203,11 +216,9 @@ def run_configs(G, args, steps: int = 20) -> dict:
         dom, bpl, launches, total = dominant(k, T, n, R)
         avg = total / launches
         passes = G.sort_plan(max(0, (R - 1).bit_length()))[0]
-        bs = survey_bytes(T, n, R, passes)
         res[name] = {"triangles": T, "npairs": n, "cells": R, "ms_per_build": round(ms, 4),
                      "us_per_build": round(ms * 1e3, 1), "Mpairs_per_s": round(n / (ms * 1e-3) / 1e6, 1),
-                     "radix_passes": passes, "bytes_survey_model": int(bs),
-                     "frac_survey_model": round(bs / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+                     **survey_fields(survey_bytes(T, n, R, passes), passes, k, steps, ms),
                      "roofline": {"kernel": dom, "avg_launch_ms": round(avg, 5), "bytes_per_launch": int(bpl),
                                   "achieved": round(bpl / (avg * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                                   "frac": round(bpl / (avg * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
@@ -301,8 +312,7 @@ def run_batched(G, args) -> dict:
                       "achieved": round(bpl / (avg * 1e-3) / 1e9, 1),
                       "peak": HBM_PEAK_GBS, "frac": round(bpl / (avg * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     res = {"ngrids": len(inputs), "triangles": int(sum(s.ntris for s in batch)), "npairs": int(ntot),
-           "cells": int(cells_tot), "bytes_survey_model": int(b_survey),
-           "frac_survey_model": round(b_survey / tb / 1e9 / HBM_PEAK_GBS, 4), "roofline": batch_roof,
+           "cells": int(cells_tot), **survey_fields(b_survey, plan[0], kern, 1, tb * 1e3), "roofline": batch_roof,
            "batched_builds_per_s": round(len(inputs) / tb, 1), "plain_builds_per_s": round(len(inputs) / tp, 1),
            "graph_builds_per_s": round(len(inputs) / tg, 1),
            "batched_ms": round(tb * 1e3, 3), "graph_ms": round(tg * 1e3, 3), "plain_ms": round(tp * 1e3, 3),
@@ -708,10 +718,8 @@ def main():
         b_alg = sum(kernel_bytes(k, T, NO, R, "finish" in kern_all) * v[0] for k, v in kern_all.items()) / args.steps
         kern_ms = sum(v[1] for v in kern_all.values()) / args.steps
         passes = G.sort_plan(max(0, (R - 1).bit_length()))[0]
-        b_survey = survey_bytes(T, NO, R, passes)
         pipeline = {"bytes_alg_per_build": int(b_alg), "frac_of_peak_at_ms_per_build": round(b_alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                    "radix_passes": passes, "bytes_survey_model": int(b_survey),
-                    "frac_survey_model": round(b_survey / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+                    **survey_fields(survey_bytes(T, NO, R, passes), passes, kern_all, args.steps, ms),
                     "kernel_ms_per_build": round(kern_ms, 4),
                     "kernels": {k: {"launches_per_build": v[0] / args.steps, "avg_ms": round(v[1] / v[0], 5)}
                                 for k, v in sorted(kern_all.items(), key=lambda kv: -kv[1][1])}}
