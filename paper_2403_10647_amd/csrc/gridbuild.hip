@@ -207,12 +207,12 @@ Plan make_plan(uint32_t bits, int max_digit = -1) {
 
 struct Layout {
   size_t ctl, hist, count_status, cull_status, cell_status, zero_end;
-  size_t grid_pairs, list_status, ntasks, list, tasks, rows, groups;  // record builds
+  size_t grid_pairs, list_status, ntasks, list, tasks, several, rows, groups;  // record builds
   size_t rec_status, zero2, zero2_end;                                // ... of a batch counted both ways
   size_t start, box, tfo, tfg, tfo_work, cull_rec, sort_status, keys_alt, vals_alt, keys_alt2, vals_alt2, run, npairs_out, splits,
       tile_grid, table, sink, kmap, ksink, total;
   uint32_t ntfo, ncount_tiles, nsort_tiles_cap, nmerge_tiles_cap;
-  uint32_t list_cap, task_lists, task_cap;
+  uint32_t list_cap, task_lists, task_cap, several_cap;
 };
 
 Layout make_layout(uint64_t ntris, uint64_t cap_pairs, uint64_t ncells_plus_grids, const Plan& plan,
@@ -338,10 +338,10 @@ bool plan_records(GridDev* grids, uint32_t ngrids, uint64_t cells, uint64_t pair
 // sizes, and the bytes the radix passes' look-back words share with those that are
 // written once the passes are done (rows only where a segment can hold several
 // chunks).  Lists of tasks: a wave adds at most four entries (and the first one
-// more), and there are no more crowded segments and long stretches than pairs and
-// segments allow.
+// more), two of them segments of several chunks, and there are no more crowded
+// segments and long stretches than pairs and segments allow.
 struct RecordSizes {
-  size_t list, list_status, ntasks, shared, rows_at, groups_at;
+  size_t list, list_status, ntasks, shared, several_at, rows_at, groups_at;
 };
 RecordSizes record_sizes(uint64_t cap_pairs, const RecordPlan& rp, Layout& L) {
   const uint32_t bits = rp.code.wx + rp.code.wy;
@@ -356,8 +356,10 @@ RecordSizes record_sizes(uint64_t cap_pairs, const RecordPlan& rp, Layout& L) {
   RecordSizes z{};
   z.list = (static_cast<size_t>(L.list_cap) + 1) * sizeof(SegEntry);
   z.list_status = (ceil_div(cap_pairs, kSegListTile) + 1) * 8;
-  z.ntasks = static_cast<size_t>(L.task_lists) * kTaskStride * 8;
-  z.rows_at = align_up(static_cast<size_t>(L.task_lists) * L.task_cap * sizeof(uint2));
+  L.several_cap = static_cast<uint32_t>(std::min<uint64_t>(ceil_div(blocks, L.task_lists) * 2, cap_pairs / (2 * kChunkPairs) + 1));
+  z.ntasks = 2 * static_cast<size_t>(L.task_lists) * kTaskStride * 8;
+  z.several_at = static_cast<size_t>(L.task_lists) * L.task_cap * sizeof(uint2);
+  z.rows_at = align_up(z.several_at + static_cast<size_t>(L.task_lists) * L.several_cap * sizeof(uint2));
   z.groups_at = z.rows_at + (chunks << bits) * 4;
   z.shared = std::max(static_cast<size_t>(rp.plan.sp.passes) * L.nsort_tiles_cap * (size_t{1} << rp.plan.rb) *
                           (narrow_words(cap_pairs) ? 4 : 8),
@@ -397,6 +399,7 @@ Layout make_record_layout(uint64_t ntris, uint64_t cap_pairs, const RecordPlan& 
   L.cull_rec = take(culled ? ntris * sizeof(CullRecord) : 0);
   L.sort_status = take(z.shared);
   L.tasks = L.sort_status;
+  L.several = L.sort_status + z.several_at;
   L.rows = L.sort_status + z.rows_at;
   L.groups = L.sort_status + z.groups_at;
   L.keys_alt = take(cap_pairs * 4);
@@ -437,6 +440,7 @@ bool make_split_layout(const Layout& P, uint64_t ntris, uint64_t cap_pairs, cons
   L.list = take(z.list);
   L.sort_status = take(z.shared);
   L.tasks = L.sort_status;
+  L.several = L.sort_status + z.several_at;
   L.rows = L.sort_status + z.rows_at;
   L.groups = L.sort_status + z.groups_at;
   *out = L;
@@ -1256,9 +1260,9 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
   a.list = sl;
   a.list_cap = b.L.list_cap;
   a.task_lists = b.L.task_lists;
-  a.task_cap = b.L.task_cap;
-  a.tasks = at<uint2>(b.ws, b.L.tasks);
-  a.ntasks = at<uint64_t>(b.ws, b.L.ntasks);
+  uint64_t* const ntasks = at<uint64_t>(b.ws, b.L.ntasks);
+  a.once = {at<uint2>(b.ws, b.L.tasks), ntasks, b.L.task_cap};
+  a.several = {at<uint2>(b.ws, b.L.several), ntasks + b.L.task_lists * kTaskStride, b.L.several_cap};
   a.rows = at<uint32_t>(b.ws, b.L.rows);
   a.groups = at<uint32_t>(b.ws, b.L.groups);
   a.ctl = ctl;
@@ -1272,15 +1276,16 @@ int launch_records_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_
     kern<<<static_cast<uint32_t>(ceil_div(std::min<uint64_t>(b.L.list_cap, npairs), kFinishRun)), kWave, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
-  if (npairs <= kOwnCountPairs) a.rows = nullptr;
-  // tasks there can be at most: chunks of crowded segments, pieces of long stretches
-  const uint64_t most = npairs / kCrowdLeast + npairs / kChunkPairs + b.code.nsegs / (kGapWave >> bits) + 1;
-  if (a.rows) {
+  if (npairs <= kOwnCountPairs) {
+    a.rows = nullptr;
+  } else {
     TraceScope ts(b.s, "finish_count");
     auto kern = b.code.wy ? finish_count_kernel<B, true> : finish_count_kernel<B, false>;
     kern<<<resident_blocks(kern, kTaskBlock, npairs / kChunkPairs), kTaskBlock, 0, b.s>>>(a);
     GB_LAUNCHED();
   }
+  // tasks there can be at most: chunks of crowded segments, pieces of long stretches
+  const uint64_t most = npairs / kCrowdLeast + npairs / kChunkPairs + b.code.nsegs / (kGapWave >> bits) + 1;
   TraceScope ts(b.s, "finish_tasks");
   auto kern = b.code.wy ? finish_tasks_kernel<B, true> : finish_tasks_kernel<B, false>;
   kern<<<resident_blocks(kern, kTaskBlock, most), kTaskBlock, 0, b.s>>>(a);

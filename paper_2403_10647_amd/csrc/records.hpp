@@ -395,6 +395,13 @@ GB_DEV uint32_t group_row_of(uint32_t pair) {
 GB_DEV uint32_t row_cells(const SegCode& c) { return 1u << (c.wx + c.wy); }
 GB_DEV uint32_t groups_of(uint32_t chunks) { return chunks < 2 * kGroupChunks ? 0u : chunks / kGroupChunks; }
 
+// Tasks of one kind: entries of what they are of, in lists of so many entries each.
+struct TaskLists {
+  uint2* entry;             // [lists][cap] (list entry | kTaskGap, its first task in this list)
+  uint64_t* n;              // [lists * kTaskStride] (zeroed) entries << 32 | tasks
+  uint32_t cap;
+};
+
 struct FinishArgs {
   GridSet gs;
   const GridRun* run;
@@ -403,10 +410,9 @@ struct FinishArgs {
   SegCode code;
   const SegEntry* list;     // [list_cap + 1]
   uint32_t list_cap;
-  uint32_t task_lists;      // lists of tasks (a power of two) ...
-  uint32_t task_cap;        // ... of so many entries each
-  uint2* tasks;             // [task_lists][task_cap] (list entry | kTaskGap, its first task in this list)
-  uint64_t* ntasks;         // [task_lists * kTaskStride] (zeroed) entries << 32 | tasks
+  uint32_t task_lists;      // lists of each kind of tasks (a power of two)
+  TaskLists once;           // segments of one chunk and empty stretches
+  TaskLists several;        // segments of several chunks
   uint32_t* rows;           // [ceil(pairs / kChunkPairs)][row_cells] a chunk's pairs per cell (null: not counted beforehand)
   uint32_t* groups;         // [ceil(pairs / (kChunkPairs * kGroupChunks))][row_cells] the same of whole groups
   Control* ctl;
@@ -494,20 +500,19 @@ GB_DEV void write_gap(const FinishArgs& a, uint32_t s0, uint32_t s1, uint32_t p,
 }
 
 // One wave: what it leaves, listed as n tasks.
-GB_DEV void list_tasks(const FinishArgs& a, uint32_t what, uint32_t n) {
+GB_DEV void list_tasks(const FinishArgs& a, const TaskLists& to, uint32_t what, uint32_t n) {
   if (lane_id() != 0) return;
   const uint32_t l = blockIdx.x & (a.task_lists - 1);
-  const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(a.ntasks + l * kTaskStride),
-                                (1ull << 32) | n);
+  const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(to.n + l * kTaskStride), (1ull << 32) | n);
   const uint32_t e = static_cast<uint32_t>(at >> 32);
-  if (e < a.task_cap) a.tasks[static_cast<uint64_t>(l) * a.task_cap + e] = make_uint2(what, static_cast<uint32_t>(at));
+  if (e < to.cap) to.entry[static_cast<uint64_t>(l) * to.cap + e] = make_uint2(what, static_cast<uint32_t>(at));
   else atomicOr(&a.ctl->error, kErrInternal);
 }
 
 // A stretch of `segs` empty segments: nothing, or listed when it is more than its wave's.
 GB_DEV void list_gap(const FinishArgs& a, uint32_t what, uint32_t segs) {
   const uint32_t per = gap_segs(a.code, kGapTask);
-  if (segs > gap_segs(a.code, kGapWave)) list_tasks(a, kTaskGap | what, segs / per + (segs % per ? 1u : 0u));
+  if (segs > gap_segs(a.code, kGapWave)) list_tasks(a, a.once, kTaskGap | what, segs / per + (segs % per ? 1u : 0u));
 }
 
 // A record as a segment's pairs see it: its cells inside the segment.
@@ -751,7 +756,7 @@ GB_DEV void finish_segment(const FinishArgs& a, uint32_t j, const SegEntry& e0, 
     const uint32_t chunks = chunks_of(n);
     uint32_t* g = a.groups + static_cast<uint64_t>(group_row_of(p0)) * row_cells(a.code);
     for (uint32_t i = lane; i < groups_of(chunks) * row_cells(a.code); i += kWave) g[i] = 0;
-    list_tasks(a, j, chunks);
+    list_tasks(a, chunks > 1 ? a.several : a.once, j, chunks);
     return;
   }
   const SegPlace pl = seg_place<Batched>(a, seg);
@@ -861,14 +866,14 @@ __global__ __launch_bounds__(kWave, 4) void finish_kernel(FinishArgs a) {
   }
 }
 
-// The tasks the waves listed, found by number: lane l holds list l's.
+// The tasks of one kind, found by number: lane l holds list l's.
 struct TaskMap {
   uint32_t entries, upto;   // the list's entries; tasks of this list and those before it
   uint32_t total;
 };
-GB_DEV TaskMap task_map(const FinishArgs& a) {
+GB_DEV TaskMap task_map(const FinishArgs& a, const TaskLists& of) {
   const uint32_t lane = lane_id();
-  const uint64_t n = lane < a.task_lists ? a.ntasks[lane * kTaskStride] : 0;
+  const uint64_t n = lane < a.task_lists ? of.n[lane * kTaskStride] : 0;
   TaskMap m;
   m.entries = static_cast<uint32_t>(n >> 32);
   m.upto = wave_inclusive(static_cast<uint32_t>(n), OpAdd{});
@@ -878,12 +883,12 @@ GB_DEV TaskMap task_map(const FinishArgs& a) {
 
 // Task t (below total): what it is of, and which of its tasks.  One whole wave;
 // a list's entries are in the order of their first tasks (one add gave both).
-GB_DEV uint32_t find_task(const FinishArgs& a, const TaskMap& m, uint32_t t, uint32_t& part) {
+GB_DEV uint32_t find_task(const TaskLists& of, const TaskMap& m, uint32_t t, uint32_t& part) {
   const uint32_t lane = lane_id();
   const uint32_t l = static_cast<uint32_t>(__popcll(ballot(m.upto <= t)));  // (below total: some list's upto exceeds t)
   if (l) t -= wave_readlane(m.upto, static_cast<int>(l - 1));
   uint32_t lo = 0, end = wave_readlane(m.entries, static_cast<int>(l));
-  const uint2* e = a.tasks + static_cast<uint64_t>(l) * a.task_cap;
+  const uint2* e = of.entry + static_cast<uint64_t>(l) * of.cap;
   while (end - lo > 1) {
     const uint32_t step = (end - lo + kWave - 1) / kWave;
     const uint32_t g = lo + lane * step;
@@ -958,21 +963,22 @@ GB_DEV uint32_t chunk_first(uint32_t r0, uint32_t r1, uint32_t chunks, uint32_t 
   return r0 + static_cast<uint32_t>(off < nr ? off : nr);
 }
 
-// The pairs per cell of every chunk of the segments that have several.
+// The pairs per cell of every chunk of the segments that have several, and of their
+// groups.  (A kernel of its own: counted by the workgroups that place them, with a
+// wait between, each row's release fence wrote back its XCD's L2, and 100k
+// hairball-like triangles in a corner took 278 us against 144.)
 template <bool Batched, bool Rows>
 __global__ __launch_bounds__(kTaskBlock) void finish_count_kernel(FinishArgs a) {
   __shared__ uint32_t s_diff[kTaskWaves * kTaskDiff];
   if (build_failed(a.ctl)) return;
-  const TaskMap map = task_map(a);
+  const TaskMap map = task_map(a, a.several);
   const uint32_t tid = threadIdx.x;
   const uint32_t w = __builtin_amdgcn_readfirstlane(tid / kWave);
   for (uint32_t t = blockIdx.x; t < map.total; t += gridDim.x) {
     uint32_t chunk;
-    const uint32_t what = find_task(a, map, t, chunk);
-    if (what & kTaskGap) continue;
-    const SegEntry e0 = a.list[what], e1 = a.list[what + 1];
+    const uint32_t j = find_task(a.several, map, t, chunk);
+    const SegEntry e0 = a.list[j], e1 = a.list[j + 1];
     const uint32_t chunks = chunks_of(e1.pair - e0.pair);
-    if (chunks == 1) continue;
     const SegPlace pl = seg_place<Batched>(a, e0.seg);
     count_chunk<Rows>(a, chunk_first(e0.rec, e1.rec, chunks, chunk), chunk_first(e0.rec, e1.rec, chunks, chunk + 1), pl.width, w,
                       s_diff + w * kTaskDiff);
@@ -1010,13 +1016,13 @@ __global__ __launch_bounds__(kTaskBlock) void finish_tasks_kernel(FinishArgs a) 
   __shared__ uint32_t s_wtot[kTaskWaves];
   static_assert(kTaskCap % 4 == 0 && kTaskCap >= kTaskWaves * kTaskDiff, "the waves' coverage fits the staging");
   if (build_failed(a.ctl)) return;
-  const TaskMap map = task_map(a);
+  const TaskMap once = task_map(a, a.once), several = task_map(a, a.several);
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t w = __builtin_amdgcn_readfirstlane(tid / kWave);
   uint32_t* const diff = s_obj + w * kTaskDiff;
-  for (uint32_t t = blockIdx.x; t < map.total; t += gridDim.x) {
+  for (uint32_t t = blockIdx.x; t < once.total + several.total; t += gridDim.x) {
     uint32_t part;
-    const uint32_t what = find_task(a, map, t, part);
+    const uint32_t what = t < once.total ? find_task(a.once, once, t, part) : find_task(a.several, several, t - once.total, part);
     if (what & kTaskGap) {
       const uint32_t j = what & ~kTaskGap, nlist = a.ctl->nlist;
       const uint32_t s0 = j == kTaskFirst ? 0u : a.list[j].seg + 1;
