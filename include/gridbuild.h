@@ -305,8 +305,9 @@ int grid_scan_u32(const uint32_t *in, const uint32_t *flags, uint32_t *out, uint
  *   "small_tiles"     1 (default): a build (or batch) whose pair capacity would
  *                     fill 16384-pair tiles on too few of the GPU's CUs, or on
  *                     little more than all of them, runs those passes in tiles
- *                     of 1024 x 8, or 512 x 16, whatever "sort_shape" says;
- *                     0: "sort_shape" always
+ *                     of 1024 x 8 (a small batch with 8-bit digits: 256 x 16),
+ *                     or 512 x 16, whatever "sort_shape" says; 0: "sort_shape"
+ *                     always
  *   "wide_lookback"   0 (default): radix passes of fewer than 2^30 pairs (by
  *                     capacity) keep 32-bit look-back words, larger ones 64-bit;
  *                     1: 64-bit words always

@@ -746,12 +746,16 @@ int pass_shape(uint64_t n, bool estimate) {
   return !estimate && tiles > cus && 2 * tiles <= 3 * cus ? 0 : 3;
 }
 
-// The sort_shape knob's, where pass_shape would take its default.  (Batches, whose
-// last pass looks each pair's grid up, are no exception.  256 x 16 / 1024 x 8, us:
-// one grid of 33K pairs 118.6 120.3, 90K 124 122, 202K 134 126; 4 grids of 24K 133.9
-// 134.7, 54K 140 138, 112K 147 140; 8 of 94K 148 141; 32 of 73K 146 140.)
-int build_sort_shape(uint64_t n, bool estimate) {
+// The sort_shape knob's, where pass_shape would take its default.  Batches, whose
+// last pass looks each pair's grid up, take 256 x 16 for few pairs where their digits
+// are 8 bits wide, a digit a thread; wider ones leave a thread two.  256 x 16 / 1024 x 8,
+// us, 8 bits: one grid of 33K pairs 117.6 119.7, 73K 119.8 121.5, 148K 120.9 121.9,
+// 299K 128.8 129.1; 8 grids of 41K 147.1 148.6, 90K 149.1 150.8, 179K 156.1 156.3; 9
+// bits: one of 41K 123.1 120.7, 139K 132.1 125.0; 8 of 50K 155.9 152.7, 71K 163.2 155.4.
+constexpr uint64_t kFewBatchPairs = uint64_t{1} << 17;
+int build_sort_shape(uint64_t n, bool estimate, bool batched = false, int digit_bits = 0) {
   const int shape = g_small_tiles ? pass_shape(n, estimate) : 3;
+  if (shape == 2 && batched && digit_bits == 8 && n <= kFewBatchPairs) return 1;
   return shape == 3 ? g_sort_shape : shape;
 }
 
@@ -1047,7 +1051,7 @@ int launch_sort_rb(Build& b, uint32_t* out_cells, uint32_t* out_objs, uint64_t n
   Control* ctl = at<Control>(b.ws, b.L.ctl);
   const uint32_t P = sp.passes;
   const bool fused = fused_first_pass(b);
-  b.sort_shape = build_sort_shape(npairs, false);  // before anything sizes or clears the passes' look-back words
+  b.sort_shape = build_sort_shape(npairs, false, B, RB);  // before anything sizes or clears the passes' look-back words
   const uint32_t* in_k = nullptr;
   const uint32_t* in_v = nullptr;
   if (fused) {
