@@ -86,12 +86,13 @@ struct RaycastArgs {
 // cells, and the objects of all those cells, one after another, are tested one
 // per lane.  What bounds it then: a turn is a chain of four dependent loads (a
 // cell's range, an object's id, its vertex indices, its vertices), and nearly
-// all of them miss L2, 73M sectors of 64 bytes for the case below; more waves
-// per SIMD are no faster (5 at 85 VGPRs: 2075 us, 6 at 79: 2196).  So the ranges
-// of several cells are loaded together, past the cell that will turn out to hold
-// the hit: 1, 2, 4, 6, 8 cells 2633, 2281, 2075, 2217, 2354 us.  1M rays over the
-// 10M-triangle arch grid: a ray per lane 4035 us, this 2132; 300k rays over a 1M
-// mesh 5906 and 674; 2000 over 5k uniform triangles 244 and 85.  Taking new rays
+// all of them miss L2, 71M lines of 128 bytes for the case below (4.3 TB/s); more waves
+// per SIMD were no faster (5 and 6 waves 2075 and 2196 us, when the walk had no
+// quotients: they are 3% of it now).  So the ranges of several cells are loaded
+// together, past the cell that will turn out to hold the hit: 1, 2, 4, 6, 8 cells
+// 2633, 2281, 2075, 2217, 2354 us (as above).  1M rays over the 10M-triangle arch
+// grid: a ray per lane 4035 us, this 2132; 300k rays over a 1M mesh 5906 and 674;
+// 2000 over 5k uniform triangles 244 and 85.  Taking new rays
 // for lanes that are done gave nothing (2% slower at 140 rays a wave).
 constexpr int kRayCells = 4;
 constexpr uint32_t kRayTests = 4096;  // most tests of one cell in a turn (a turn's slots are 32 bits)
