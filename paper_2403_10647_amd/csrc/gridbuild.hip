@@ -877,8 +877,8 @@ int launch_compact(Build& b, const grid_out* out) {
 // The path a plain build takes when it is left to the statistics (knob
 // build_path = 2): the compact path's atomics cost more per pair than the
 // sorted path's passes, so it only pays where launches dominate, small sparse
-// grids (measured on MI355X: 0.78-0.90 of the sorted time up to 150K pairs,
-// 1.24 at 0.9M, 3.7-10 beyond).
+// grids (compact over sorted, pairs: 1.01-1.17 17K, where the sort takes one pass by
+// records, 0.95 28K, 0.87 150K, 1.4 0.9M, 5.6-18 beyond).
 int choose_path(uint64_t npairs, uint64_t ncells) {
   if (npairs == 0) return 0;
   return npairs <= kCompactMaxPairs && static_cast<double>(npairs) <= kCompactMaxPairsPerCell * ncells ? 1 : 0;
